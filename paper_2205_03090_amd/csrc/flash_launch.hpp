@@ -62,8 +62,7 @@ __device__ __forceinline__ uint32_t stage_id(const Ctx<NC> &c, int64_t k)
     return c.L.ids[l1][k];
 }
 
-// Ids a wavefront claims from a stage's input with one atomic (after its
-// static first share, three quarters of an even split of the input).
+// Ids a wavefront claims from a stage's input with one atomic at most.
 constexpr int kChunk = 64;
 // Per-wavefront staging of list appends in LDS (entries per output list).
 constexpr int kStage = 512;
@@ -94,24 +93,42 @@ __device__ __forceinline__ unsigned long long bcast64(unsigned long long v, int 
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Input positions a wavefront takes from its stage's input.  First its
-// static share, a contiguous range of three quarters of the input split
-// evenly (consecutive lanes take consecutive positions, which keeps the
-// mixtures a wavefront touches, and the records it reads, close together in
-// memory); then chunks of kChunk positions from the stage's counter, one
-// atomic per chunk.
+// Input positions a wavefront of SLOTS concurrent items (64, or 64/G with
+// groups of G lanes) takes from its stage's input.  First its static share, a
+// contiguous range (consecutive lanes take consecutive positions, which keeps
+// the mixtures a wavefront touches, and the records it reads, close together in
+// memory); then chunks from the stage's counter, one atomic per chunk.
+//
+// One item per lane: three quarters of the input are static and a chunk is
+// kChunk positions, one per lane.  Smaller chunks cost more than they balance
+// (all wavefronts claim at about the same time and the atomics on one counter
+// serialise: 500,000 stability analyses at nc 8 took 1.22 ms with 64, 1.32 with
+// 32 and 1.39 with 8).
+//
+// Groups: a wavefront holds two or four items, whose step counts vary by an
+// order of magnitude, so a static share or a chunk of dozens of positions is a
+// long private queue that the other wavefronts wait for.  One eighth is static
+// and a chunk is a quarter of the wavefront's even share of what was left when
+// it last claimed, at least one position per slot: 400,000 mixtures at nc 20
+// took 14.65 ms with the shares of the lane form, 10.6 ms with these (11.0 with
+// three quarters static), a ragged batch of 500,000 23.3 and 15.5 ms.
+template <int SLOTS>
 struct Claim {
+    static constexpr bool kGuided = SLOTS < 64;
     unsigned long long nw, wid, s0, sj, dyn0, cb, ce;   // [cb, ce): claimed, not yet taken
+    unsigned long long dyn, left;   // dynamic positions; unclaimed at the last claim
 
     __device__ __forceinline__ Claim(int64_t count, unsigned long long nw_,
                                      unsigned long long wid_)
         : nw(nw_), wid(wid_), sj(0), cb(0), ce(0)
     {
-        s0 = (unsigned long long)(count > 0 ? count : 0) * 3ull / 4ull / nw;
+        const unsigned long long n = (unsigned long long)(count > 0 ? count : 0);
+        s0 = (kGuided ? n / 8ull : n * 3ull / 4ull) / nw;
         dyn0 = nw * s0;
+        dyn = left = n - dyn0;
     }
 
-    // Called by every lane of the wavefront with the number r (1..64) of
+    // Called by every lane of the wavefront with the number r (1..SLOTS) of
     // takers; returns the position for the taker of rank `rank` (used in
     // the taker lanes only).
     __device__ __forceinline__ unsigned long long next(int r, unsigned long long rank, int lane,
@@ -119,10 +136,16 @@ struct Claim {
     {
         const unsigned long long ru = (unsigned long long)r;
         const unsigned long long as = s0 - sj, ad = ce - cb;
-        unsigned long long nb = 0;
+        unsigned long long nb = 0, size = kChunk;
         if (as + ad < ru) {
-            if (lane == 0) nb = dyn0 + atomicAdd(take, (unsigned long long)kChunk);
+            if constexpr (kGuided) {
+                size = left / (4ull * nw);
+                size = size < SLOTS ? SLOTS : size > kChunk ? kChunk : size;
+            }
+            if (lane == 0) nb = atomicAdd(take, size);
             nb = bcast64(nb, 0);
+            if constexpr (kGuided) left = dyn > nb + size ? dyn - (nb + size) : 0;
+            nb += dyn0;
         }
         unsigned long long k;
         if (rank < as) k = wid * s0 + sj + rank;
@@ -137,7 +160,7 @@ struct Claim {
                 cb += rem;
             } else {
                 cb = nb + (rem - ad);
-                ce = nb + kChunk;
+                ce = nb + size;
             }
         }
         return k;
@@ -202,8 +225,7 @@ __device__ __forceinline__ void append_slot(const Lists &L, int list, int l, uin
 }
 
 // Persistent stage: one item per lane; lanes whose item finished take the
-// next input positions of the wavefront (Claim: a static share, then
-// chunks of kChunk from the stage's counter).  The
+// next input positions of the wavefront (Claim).  The
 // list entries the steps produce are staged per wavefront in LDS and
 // appended kStage at a time (one atomic per batch).  Every item finishes
 // within its stage's iteration caps (and kStepGuard steps), so every
@@ -224,7 +246,7 @@ stage_persistent(Ctx<NC> c, const double *__restrict__ Tc, const double *__restr
     int fill[NOUT];
 #pragma unroll
     for (int l = 0; l < NOUT; ++l) fill[l] = 0;
-    Claim cl(count, (unsigned long long)gridDim.x * (blockDim.x / 64),
+    Claim<64> cl(count, (unsigned long long)gridDim.x * (blockDim.x / 64),
              (unsigned long long)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64);
     Item it;
     bool live = false, gone = false;
@@ -300,7 +322,7 @@ stage_persistent_group(Ctx<NC> c, const double *__restrict__ Tc, const double *_
     int fill[NOUT];
 #pragma unroll
     for (int l = 0; l < NOUT; ++l) fill[l] = 0;
-    Claim cl(count, (unsigned long long)gridDim.x * (blockDim.x / 64),
+    Claim<64 / G> cl(count, (unsigned long long)gridDim.x * (blockDim.x / 64),
              (unsigned long long)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64);
     Item it;
     bool live = false, gone = false;   // the same in every lane of a group
