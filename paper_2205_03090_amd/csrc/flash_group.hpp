@@ -188,7 +188,7 @@ __device__ __forceinline__ void phase_derivs_g(double &hdiag, const PhaseG &o,
     const double dL = (Z * dB - B * dZ) * izzb;
     const double be = (dZ - dB) * izb;
     const double ga = 2.0 * (dL - L * dB * ib) * ib;
-    const double al = (dZ + (dA * L + A * dL) * ib - A * L * dB * ib * ib) * ib - o.q1 * dB * ib;
+    const double al = (dZ + fma(dA, L, A * dL) * ib - A * L * dB * ib * ib) * ib - o.q1 * dB * ib;
     double *va = g.vec(0), *vb = g.vec(1), *vg = g.vec(2), *vs = g.vec(3), *vv = g.vec(4);
     va[g.gi] = al;
     vb[g.gi] = be;
@@ -842,8 +842,7 @@ struct SaTrGroup {
         double dinv = 0.0, u;
         bool eta0;
         double pr = trust_step_g<NC, G>(u, rad, eta0, dinv, hdiag, dadd, gv, g, fl);
-        const double bi = 2.0 * sqrt(W);
-        const double amax = gmin<G>((g.act && u < 0.0) ? fmin(1.0, 0.99 * bi / -u) : 1.0);
+        const double amax = gmin<G>((g.act && u < 0.0) ? cut_step(1.0, 2.0 * sqrt(W), -u) : 1.0);
         slen = amax * sqrt(gsum<G>(g.act ? u * u : 0.0));
         if (amax < 1.0) {
             const double gu = gsum<G>(gv * u);
@@ -1173,9 +1172,8 @@ struct SpNtGroup {
             }
             if (spol) {
                 u *= vs;
-                double lim = 1.0;
-                if (g.act && u < 0.0) lim = fmin(lim, 0.99 * v0 / -u);
-                if (g.act && u > 0.0) lim = fmin(lim, 0.99 * (z - v0) / u);
+                // inactive lanes hold u = 0
+                const double lim = cut_step(1.0, u < 0.0 ? v0 : z - v0, fabs(u));
                 const double dmax = gmax<G>(fabs(u));
                 const double amax = gmin<G>(lim);
                 v0 += amax * u;
@@ -1193,9 +1191,8 @@ struct SpNtGroup {
             // dn = v o u, kept inside 0 < n^V < z
             const double nu = sqrt(gsum<G>(g.act ? u * u : 0.0));
             u *= vs;
-            double lim = 1.0;
-            if (g.act && u < 0.0) lim = fmin(lim, 0.99 * v0 / -u);
-            if (g.act && u > 0.0) lim = fmin(lim, 0.99 * (z - v0) / u);
+            // inactive lanes hold u = 0
+            const double lim = cut_step(1.0, u < 0.0 ? v0 : z - v0, fabs(u));
             const double amax = gmin<G>(lim);
             if (amax < 1.0) {
                 const double gu = gsum<G>(gt * u);

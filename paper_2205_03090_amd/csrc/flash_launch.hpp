@@ -506,7 +506,10 @@ eval_phase_kernel(int64_t n, const double *__restrict__ c, const double *__restr
 // ---------------------------------------------------------------------------
 // Backward (implicit function theorem on the converged split)
 // ---------------------------------------------------------------------------
-
+// The phase evaluations here keep the form (EACH, FIX false) whose roundings
+// this kernel has always had: the gradient divides by x_j, which next to a zero
+// component scales a last bit up without limit, and the kernel is a twentieth of
+// a training step (0.13 of 2.8 ms at 300,000 mixtures and nc 10).
 
 template <int NC, bool PM>
 __global__ void __launch_bounds__(kBlock)
@@ -567,9 +570,9 @@ flash_backward_kernel(BwdArgs a, const double *__restrict__ Tc0, const double *_
         eos_setup<NC>(e, Tc, Pc, om, T, P);
         uint32_t fl = 0;
         Phase<NC> oL, oV;
-        phase_eval<NC>(oL, e, K, x, fl);
+        phase_eval<NC, true>(oL, e, K, x, fl);
         double Phi[NP];
-        phase_derivs<NC>(Phi, oL, e, K, fl);
+        phase_derivs<NC, false>(Phi, oL, e, K, fl);
         // z~_bar_j = [gx_j + lambda_j/x_j - sum lambda + (Phi^L lambda)_j]/(1 - beta)
         double sl = 0.0;
 #pragma unroll
@@ -583,7 +586,7 @@ flash_backward_kernel(BwdArgs a, const double *__restrict__ Tc0, const double *_
         }
         PhaseGrad<NC> gL, gV;
         phase_param_vjp<NC>(gL, oL, e, x, lam, K, Tc, om, T, P);
-        phase_eval<NC>(oV, e, K, y, fl);
+        phase_eval<NC, true>(oV, e, K, y, fl);
         phase_param_vjp<NC>(gV, oV, e, y, lam, K, Tc, om, T, P);
         gT = -(gV.dT - gL.dT);
         gP = -(gV.dP - gL.dP);

@@ -80,6 +80,25 @@ struct Phase {
     int nroots;
 };
 
+// Sign of the Gibbs energy difference gv - gl of two roots zl <= zv of the
+// cubic (g as in cubic_root): -1 or 1 where single precision decides it, 0
+// where the two are too close for that, not finite, or so small that a
+// single-precision operand could be subnormal.  Every single-precision operand
+// is a rounded FP64 value or a ratio of two, so l1 and l2 carry absolute errors
+// of about 4e-7 (1 + |l|); the margin is over ten times the resulting error of d.
+__device__ __forceinline__ int gibbs_order(double A, double B, double zl, double zv)
+{
+    if (!(zl - B > 1e-30)) return 0;
+    const float l1 = logf((float)(zv - B) / (float)(zl - B));
+    const float l2 = logf((float)(zl * (zv + B)) / (float)(zv * (zl + B)));
+    const float ab = (float)A / (float)B;
+    const float d = (float)(zv - zl) - l1 - ab * l2;
+    const float tol = 2e-5f * (1.0f + fabsf(l1) + ab);
+    if (d > tol) return 1;
+    if (d < -tol) return -1;
+    return 0;
+}
+
 // Minimum-Gibbs root of Z^3 - Z^2 + (A - B - B^2) Z - AB = 0 (eq. cubic_Z).
 // Halley's iteration (eq. halley) from the liquid-like start Z = B (or from
 // zs, the root chosen at the previous iterate of the same phase, when it lies
@@ -93,6 +112,7 @@ struct Phase {
 // correction on the full cubic; between the smallest (liquid) and largest
 // (vapour) root the one with the lower reduced residual Gibbs energy
 // g = Z - 1 - ln(Z - B) - (A/B) ln(1 + B/Z) is kept (ties go to the liquid).
+template <bool EACH = false>
 __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, double &Lout,
                                            double &lzbout, int &nroots, uint32_t &fl,
                                            double zs = -1.0)
@@ -145,25 +165,59 @@ __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, dou
         const double d = f / fp;
         return (fabs(d) < 1e-3 * z0) ? z0 - d : z0;
     };
-    if (nroots > 1) {
-        zl = pol(zl);
-        zv = pol(zv);
-        fl += 2 * Cost<1>::polish;
-        const double lzl = log(zl - B), ll = log1p(B / zl);
-        const double lzv = log(zv - B), lv = log1p(B / zv);
-        const double ab = A / B;
-        const double gl = zl - 1.0 - lzl - ab * ll;
-        const double gv = zv - 1.0 - lzv - ab * lv;
-        fl += 2 * Cost<1>::gibbs;
-        if (gv < gl) { Zout = zv; Lout = lv; lzbout = lzv; }
-        else { Zout = zl; Lout = ll; lzbout = lzl; }
-    } else {
-        Z = pol(Z);
-        fl += Cost<1>::polish + 4;
-        Zout = Z;
-        Lout = log1p(B / Z);
-        lzbout = log(Z - B);
+    if constexpr (EACH) {
+        // each branch forms the logarithms of its own root or roots (the
+        // adjoint, see flash_backward_kernel)
+        if (nroots > 1) {
+            zl = pol(zl);
+            zv = pol(zv);
+            fl += 2 * Cost<1>::polish;
+            const double lzl = log(zl - B), ll = log1p(B / zl);
+            const double lzv = log(zv - B), lv = log1p(B / zv);
+            const double ab = A / B;
+            const double gl = zl - 1.0 - lzl - ab * ll;
+            const double gv = zv - 1.0 - lzv - ab * lv;
+            fl += 2 * Cost<1>::gibbs;
+            if (gv < gl) { Zout = zv; Lout = lv; lzbout = lzv; }
+            else { Zout = zl; Lout = ll; lzbout = lzl; }
+        } else {
+            Z = pol(Z);
+            fl += Cost<1>::polish + 4;
+            Zout = Z;
+            Lout = log1p(B / Z);
+            lzbout = log(Z - B);
+        }
+        return;
     }
+    // The polished candidates, the choice between them, and then one call site
+    // each for ln(Z - B) and ln(1 + B/Z) of the chosen root.  The two FP64
+    // logarithms are the longest sequences of a phase evaluation (about 410 and
+    // 570 cycles of the issue port against 110 for an exp), and a wavefront
+    // with a lane of three roots (a quarter to a half of them, at 0.5-3 % of
+    // the evaluations) ran them three times: both candidates, and the single
+    // root in the other branch.  The choice needs only the sign of gv - gl,
+    // which single precision decides in all but 1e-5 of the evaluations; only
+    // there are the candidates' energies formed in FP64.  10^6 mixtures at
+    // nc 8: 3.80 -> 3.67 ms.
+    zl = pol(zl);
+    bool vapour = false;
+    if (nroots > 1) {
+        zv = pol(zv);
+        fl += 2 * Cost<1>::polish + 2 * Cost<1>::gibbs;
+        int sg = gibbs_order(A, B, zl, zv);
+        if (sg == 0) {
+            const double ab = A / B;
+            const double gl = zl - 1.0 - log(zl - B) - ab * log1p(B / zl);
+            const double gv = zv - 1.0 - log(zv - B) - ab * log1p(B / zv);
+            sg = gv < gl ? -1 : 1;
+        }
+        vapour = sg < 0;
+    } else {
+        fl += Cost<1>::polish + 4;
+    }
+    Zout = vapour ? zv : zl;
+    Lout = log1p(B / Zout);
+    lzbout = log(Zout - B);
 }
 
 // Fugacity coefficients of one phase (eq. lnphi) for mole numbers w (any
@@ -172,15 +226,13 @@ __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, dou
 //   ln phi_i = B_i q1 - ln(Z - B) - q2 s_i psi'_i,
 //   q1 = (Z - 1 + (A/B) L)/B,  q2 = 2L/B,  L = ln(1 + B/Z).
 // K points at the shared nc*nc k_ij table (compile-time indexed, so that the
-// loads are wave-uniform).
-template <int NC>
-__device__ __forceinline__ void phase_eval(Phase<NC> &o, const Eos<NC> &e,
-                                           const double *__restrict__ K, const double (&w)[NC],
-                                           uint32_t &fl, double zs = -1.0)
+// loads are wave-uniform).  sum is the sum of w.
+template <int NC, bool EACH = false>
+__device__ __forceinline__ void phase_eval_sum(Phase<NC> &o, const Eos<NC> &e,
+                                               const double *__restrict__ K,
+                                               const double (&w)[NC], double sum, uint32_t &fl,
+                                               double zs)
 {
-    double sum = 0.0;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) sum += w[i];
     const double inv = 1.0 / sum;
     double c[NC], t[NC], S = 0.0;
 #pragma unroll
@@ -206,7 +258,7 @@ __device__ __forceinline__ void phase_eval(Phase<NC> &o, const Eos<NC> &e,
         B += c[i] * e.b[i];
     }
     fl += Cost<NC>::mix;
-    cubic_root(A, B, o.Z, o.L, o.lzb, o.nroots, fl, zs);
+    cubic_root<EACH>(A, B, o.Z, o.L, o.lzb, o.nroots, fl, zs);
     o.A = A;
     o.B = B;
     const double ib = 1.0 / B;
@@ -215,6 +267,17 @@ __device__ __forceinline__ void phase_eval(Phase<NC> &o, const Eos<NC> &e,
 #pragma unroll
     for (int i = 0; i < NC; ++i) o.lnphi[i] = e.b[i] * o.q1 - o.lzb - o.q2 * e.s[i] * o.psi[i];
     fl += Cost<NC>::lnphi;
+}
+
+template <int NC, bool EACH = false>
+__device__ __forceinline__ void phase_eval(Phase<NC> &o, const Eos<NC> &e,
+                                           const double *__restrict__ K, const double (&w)[NC],
+                                           uint32_t &fl, double zs = -1.0)
+{
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) sum += w[i];
+    phase_eval_sum<NC, EACH>(o, e, K, w, sum, fl, zs);
 }
 
 // Unit-mole composition derivatives Phi_ij = n d ln phi_i / d n_j at fixed
@@ -227,7 +290,10 @@ __device__ __forceinline__ void phase_eval(Phase<NC> &o, const Eos<NC> &e,
 // and differentiating ln phi_i = B_i q1 - ln(Z - B) - q2 s_i psi'_i:
 //   Phi_ij = B_i D_j q1 - D_j ln(Z-B) - s_i psi'_i D_j q2
 //            + q2 s_i psi'_i - q2 s_i (1 - k_ij) s_j.
-template <int NC>
+// One sum of two products has its rounding fixed (FIX): left to the compiler,
+// which of the two is fused depends on the code around it, and with it the last
+// bit of the result.
+template <int NC, bool FIX = true>
 __device__ __forceinline__ void phase_derivs(double (&Phi)[Tri<NC>::N], const Phase<NC> &o,
                                              const Eos<NC> &e, const double *__restrict__ K,
                                              uint32_t &fl)
@@ -250,7 +316,8 @@ __device__ __forceinline__ void phase_derivs(double (&Phi)[Tri<NC>::N], const Ph
         const double dL = (Z * dB - B * dZ) * izzb;
         be[j] = (dZ - dB) * izb;
         ga[j] = 2.0 * (dL - L * dB * ib) * ib;
-        al[j] = (dZ + (dA * L + A * dL) * ib - A * L * dB * ib * ib) * ib - o.q1 * dB * ib;
+        const double dAL = FIX ? fma(dA, L, A * dL) : dA * L + A * dL;
+        al[j] = (dZ + dAL * ib - A * L * dB * ib * ib) * ib - o.q1 * dB * ib;
     }
 #pragma unroll
     for (int i = 0; i < NC; ++i)
