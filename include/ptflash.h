@@ -85,7 +85,10 @@ extern "C" {
                                      lanes.  With grid, block and the lanes
                                      options all 0, a batch of n mixtures runs
                                      as FUSED when n <= 150000 (nc <= 8) or
-                                     n * nc <= 400000 (nc > 8)            */
+                                     n * nc <= 400000 (nc > 8), the smallest
+                                     of these with a team of lanes per mixture
+                                     (n <= 24000 at nc <= 4, n <= 12000 up to
+                                     nc = 12)                             */
 #define PTFLASH_FORM_PLAIN 1      /* one launch per stage iteration + compaction */
 #define PTFLASH_FORM_FUSED 2      /* one launch; a lane pair carries one mixture
                                      through every stage, its two stability

@@ -23,6 +23,7 @@
 #include "flash_api.hpp"
 #include "flash_stages.hpp"
 #include "flash_group.hpp"
+#include "flash_team.hpp"
 #include "adjoint_device.hpp"
 #include "tuned_gfx950.hpp"
 
@@ -420,6 +421,40 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     if (o.l0 == L_SPLIT) {
         fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
         if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
+    }
+}
+
+// The fused form with a team of lanes per mixture (flash_team.hpp): as
+// stage_fused, for batches that leave most of the device idle.  per_wave
+// mixtures per wavefront, at most Team::kPerWave: fewer where the batch is
+// small enough to give every wavefront less, since the mixtures of a wavefront
+// wait for each other.  Blocks are one wavefront.
+template <int NC, bool PM, class X>
+__global__ void __launch_bounds__(64)
+stage_team(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__ Pc,
+           const double *__restrict__ om, const double *__restrict__ K, int per_wave)
+{
+    c.pr = Props{Tc, Pc, om, K};
+    const int slot = (int)threadIdx.x / X::kLanes;
+    const int64_t m = (int64_t)blockIdx.x * per_wave + slot;
+    if (slot >= per_wave || m >= c.a.n) return;   // whole teams
+    const uint32_t t = threadIdx.x & 1u;
+    const uint32_t id = (uint32_t)m;
+    Outbox o;
+    fused_item<FeedItem<NC, PM, X>, NC>(c, id, o);
+    if (o.l0 == L_PRE) fused_item<PreSsItem<NC, PM, X>, NC>(c, id, o);
+    if (o.l0 == L_SA) {
+        // trial t by the lanes of parity t, then the decision
+        Outbox q;
+        fused_item<SaSsItem<NC, PM, X>, NC>(c, 2 * id + t, q);
+        if (q.l0 == L_SATR) fused_item<SaTrItem<NC, PM, X>, NC>(c, 2 * id + t, q);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        fused_item<SaFinItem<NC, PM>, NC>(c, id, o);
+    }
+    if (c.a.stability_only) return;
+    if (o.l0 == L_SPLIT) {
+        fused_item<SpSsItem<NC, PM, X>, NC>(c, id, o);
+        if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM, X>, NC>(c, id, o);
     }
 }
 
@@ -822,6 +857,11 @@ int lanes_ss(const ptflash_options *o, bool pm)
     return lanes_ok<NC>(o->lanes_ss > 0 ? o->lanes_ss : tuned_lanes_ss(NC, pm));
 }
 
+template <int NC, bool PM> using SaSsSolo = SaSsItem<NC, PM>;
+template <int NC, bool PM> using SaTrSolo = SaTrItem<NC, PM>;
+template <int NC, bool PM> using SpSsSolo = SpSsItem<NC, PM>;
+template <int NC, bool PM> using SpNtSolo = SpNtItem<NC, PM>;
+
 // One stage with a group form (Item1: one mixture per lane; ItemG<G>:
 // groups).
 template <template <int, bool> class Item1, template <int, bool, int> class ItemG, int NC,
@@ -854,12 +894,12 @@ int launch_persistent(const FlashArgs &a, const ptflash_problem *p, const ptflas
     int rc;
     if ((rc = run_persistent_stage<FeedItem<NC, PM>, NC>(c, p, o, kTake0 + 0, s))) return rc;
     if ((rc = run_persistent_stage<PreSsItem<NC, PM>, NC>(c, p, o, kTake0 + 1, s))) return rc;
-    if ((rc = run_tr_stage<SaSsItem, SaSsGroup, NC, PM>(c, p, o, lss, kTake0 + 2, s))) return rc;
-    if ((rc = run_tr_stage<SaTrItem, SaTrGroup, NC, PM>(c, p, o, lsa, kTake0 + 3, s))) return rc;
+    if ((rc = run_tr_stage<SaSsSolo, SaSsGroup, NC, PM>(c, p, o, lss, kTake0 + 2, s))) return rc;
+    if ((rc = run_tr_stage<SaTrSolo, SaTrGroup, NC, PM>(c, p, o, lsa, kTake0 + 3, s))) return rc;
     if ((rc = run_persistent_stage<SaFinItem<NC, PM>, NC>(c, p, o, kTake0 + 4, s))) return rc;
     if (a.stability_only) return PTFLASH_OK;
-    if ((rc = run_tr_stage<SpSsItem, SpSsGroup, NC, PM>(c, p, o, lss, kTake0 + 5, s))) return rc;
-    if ((rc = run_tr_stage<SpNtItem, SpNtGroup, NC, PM>(c, p, o, lsp, kTake0 + 6, s))) return rc;
+    if ((rc = run_tr_stage<SpSsSolo, SpSsGroup, NC, PM>(c, p, o, lss, kTake0 + 5, s))) return rc;
+    if ((rc = run_tr_stage<SpNtSolo, SpNtGroup, NC, PM>(c, p, o, lsp, kTake0 + 6, s))) return rc;
     return PTFLASH_OK;
 }
 
@@ -926,6 +966,39 @@ int launch_fused(const FlashArgs &a, const ptflash_problem *p, const ptflash_opt
     return hipGetLastError() == hipSuccess ? PTFLASH_OK : PTFLASH_EHIP;
 }
 
+// Batches up to this many mixtures run the fused form with a team of lanes per
+// mixture (0: never).  A team takes 8 or 16 lanes where the lane pair takes two
+// and needs about half the instructions per step, so it wins while the device has
+// lanes to spare.  Measured (MI355X, us per call, lane pair against team): nc 3
+// 295 / 196 at 1000 mixtures, 336 / 258 at 12,000, 300 / 304 at 24,000, 399 / 603 at
+// 60,000; nc 8 503 / 262 at 1000, 753 / 630 at 12,000, 742 / 648 at 16,000, 806 / 811
+// at 24,000; nc 5 452 / 260, 511 / 466 at 12,000, 556 / 636 at 16,000; nc 12 (own
+// sets) 1574 / 1005, 1562 / 1509 at 12,000.  Above nc 12 a lane's matrices spill in
+// either form and the team gains nothing reliably.
+template <int NC>
+constexpr int64_t team_max_n()
+{
+    return NC <= 4 ? 24000 : NC <= 12 ? 12000 : 0;
+}
+
+template <int NC, bool PM>
+int launch_team(const FlashArgs &a, const ptflash_problem *p, void *ws, hipStream_t s)
+{
+    using X = Team<(NC <= 4 ? 4 : 8)>;
+    Ctx<NC> c;
+    char *tail;
+    setup_ctx<NC>(c, a, p->n, ws, &tail);
+    // one wavefront per SIMD before a wavefront takes a second mixture
+    constexpr int64_t kSimds = 1024;
+    const int64_t need = (p->n + kSimds - 1) / kSimds;
+    const int64_t per_wave = need < X::kPerWave ? need : X::kPerWave;
+    if (per_wave > 0)
+        hipLaunchKernelGGL((stage_team<NC, PM, X>),
+                           dim3((unsigned)((p->n + per_wave - 1) / per_wave)), dim3(64), 0, s, c,
+                           p->Tc, p->Pc, p->omega, p->kij, (int)per_wave);
+    return hipGetLastError() == hipSuccess ? PTFLASH_OK : PTFLASH_EHIP;
+}
+
 template <int NC, bool PM>
 int launch_plain(const FlashArgs &a, const ptflash_problem *p, void *ws, hipStream_t s)
 {
@@ -986,6 +1059,9 @@ int nc_flash_pm(const FlashArgs &a, const ptflash_problem *p, const ptflash_opti
     if (o->form == PTFLASH_FORM_FUSED) return launch_fused<NC, PM>(a, p, o, ws, s);
     if (o->grid <= 0 && o->block <= 0 && o->lanes_per_mixture <= 0 && o->lanes_split <= 0 &&
         o->lanes_ss <= 0 && p->n <= fused_max_n<NC>()) {
+        if constexpr (team_max_n<NC>() > 0) {
+            if (p->n <= team_max_n<NC>()) return launch_team<NC, PM>(a, p, ws, s);
+        }
         ptflash_options f = *o;
         f.block = 64;
         return launch_fused<NC, PM>(a, p, &f, ws, s);

@@ -183,6 +183,19 @@ struct Outbox {
     }
 };
 
+// How the items below use the lanes of a wavefront.  Solo: an item is one
+// lane's work.  (A team of lanes per item: flash_team.hpp.)  map and its
+// relatives apply a function to every element of a per-component array.
+struct Solo {
+    static constexpr bool kTeam = false;
+    template <int NC, class F>
+    static __device__ __forceinline__ void map(double (&v)[NC], F f)
+    {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) v[i] = f(v[i]);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Shared helpers
 // ---------------------------------------------------------------------------
@@ -246,21 +259,32 @@ __device__ __forceinline__ void write_outputs_unstable(const Ctx<NC> &c, int64_t
 
 // K -> Rachford-Rice -> x, y (x_i = z_i/(1 + th(K_i - 1)), y_i = K_i x_i) and
 // the factors ix, iy that normalise them.  False when no root exists.
-template <int NC>
+template <int NC, class X = Solo>
 __device__ __forceinline__ bool raw_xy_from_lnk(double (&x)[NC], double (&y)[NC], double &ix,
                                                 double &iy, const double (&lnk)[NC],
                                                 const double (&z)[NC], double &theta,
                                                 uint32_t &fl)
 {
     double K[NC];
+    if constexpr (X::kTeam) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) K[i] = exp(lnk[i]);
+        for (int i = 0; i < NC; ++i) K[i] = lnk[i];
+        X::template map<NC>(K, [](double v) { return exp(v); });
+    } else {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) K[i] = exp(lnk[i]);
+    }
     fl += NC;
     if (!rr_solve<NC>(z, K, theta, fl)) return false;
     double sx = 0.0, sy = 0.0;
+    if constexpr (X::kTeam) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) y[i] = 1.0 + theta * (K[i] - 1.0);
+        X::template map2<NC>(x, z, y, [](double p, double q) { return p / q; });
+    }
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-        x[i] = z[i] / (1.0 + theta * (K[i] - 1.0));
+        if constexpr (!X::kTeam) x[i] = z[i] / (1.0 + theta * (K[i] - 1.0));
         y[i] = K[i] * x[i];
         sx += x[i];
         sy = fma(K[i], x[i], sy);
@@ -290,13 +314,13 @@ __device__ __forceinline__ double scale_sum(double (&w)[NC], double f)
 }
 
 // The same, normalised.
-template <int NC>
+template <int NC, class X = Solo>
 __device__ __forceinline__ bool xy_from_lnk(double (&x)[NC], double (&y)[NC],
                                             const double (&lnk)[NC], const double (&z)[NC],
                                             double &theta, uint32_t &fl)
 {
     double ix, iy;
-    if (!raw_xy_from_lnk<NC>(x, y, ix, iy, lnk, z, theta, fl)) return false;
+    if (!raw_xy_from_lnk<NC, X>(x, y, ix, iy, lnk, z, theta, fl)) return false;
 #pragma unroll
     for (int i = 0; i < NC; ++i) { x[i] *= ix; y[i] *= iy; }
     return true;
@@ -377,12 +401,19 @@ __device__ __forceinline__ double ss_update(double (&v)[NC], double (&prev)[NC],
 // Feed: input checks, EOS constants, feed evaluation, Wilson K and the first
 // Rachford-Rice decision of the initial substitutions (Sec. 2.2.1, 2.2.3)
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 __device__ __forceinline__ void wilson_lnk(double (&lk)[NC], const Props &pr, double T, double P)
 {
+    if constexpr (X::kTeam) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-        lk[i] = log(pr.Pc[i] / P) + kWilson * (1.0 + pr.om[i]) * (1.0 - pr.Tc[i] / T);
+        for (int i = 0; i < NC; ++i) lk[i] = pr.Pc[i] / P;
+        X::template map<NC>(lk, [](double v) { return log(v); });
+    }
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const double l = X::kTeam ? lk[i] : log(pr.Pc[i] / P);
+        lk[i] = l + kWilson * (1.0 + pr.om[i]) * (1.0 - pr.Tc[i] / T);
+    }
 }
 
 // The record fields every later stage reads, and the routing of a mixture
@@ -413,7 +444,7 @@ __device__ __forceinline__ void route_mixture(MixRec<NC> &r, Outbox &ob, int64_t
     }
 }
 
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct FeedItem {
     static constexpr int WAVES = 1;   // minimum wavefronts per SIMD
     static constexpr bool kPerMixture = PM;   // one component set per mixture
@@ -488,11 +519,17 @@ struct FeedItem {
 #pragma unroll
             for (int i = 0; i < NC; ++i) ls[i] = a.lnk0[m * NC + i];
         } else {
-            wilson_lnk<NC, PM>(ls, pp, T, P);
+            wilson_lnk<NC, PM, X>(ls, pp, T, P);
+        }
+        double lnz[NC];
+        if constexpr (X::kTeam) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) lnz[i] = z[i];
+            X::template map<NC>(lnz, [](double v) { return log(v); });
         }
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const double lz = log(z[i]);
+            const double lz = X::kTeam ? lnz[i] : log(z[i]);
             r.s[i] = e.s[i];
             r.b[i] = e.b[i];
             r.lnz[i] = lz;
@@ -515,7 +552,7 @@ struct FeedItem {
         // case 1 here; the other mixtures repeat it in PreSs
         double x[NC], y[NC], theta = 0.5;
         uint32_t frr = 0;
-        const bool in = xy_from_lnk<NC>(x, y, ls, z, theta, frr) && theta > 0.0 && theta < 1.0;
+        const bool in = xy_from_lnk<NC, X>(x, y, ls, z, theta, frr) && theta > 0.0 && theta < 1.0;
         if (!in) {
             route_mixture<NC>(r, ob, m, false, kStSaRan, fl + frr, 0, ls, theta);
         } else {
@@ -532,7 +569,7 @@ struct FeedItem {
 // PreSs: the initial phase-split substitutions and the triage (Sec. 2.2.3)
 // of the mixtures that Feed did not send to case 1
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct PreSsItem {
     static constexpr int WAVES = 1;   // minimum wavefronts per SIMD
     static constexpr bool kPerMixture = PM;   // one component set per mixture
@@ -573,34 +610,43 @@ struct PreSsItem {
         const FlashArgs &a = c.a;
         MixRec<NC> &r = c.rec[m];
         double w0[NC], w1[NC], ix, iy;
-        if (!(raw_xy_from_lnk<NC>(w0, w1, ix, iy, lk, z, theta, fl) && theta > 0.0 &&
+        if (!(raw_xy_from_lnk<NC, X>(w0, w1, ix, iy, lk, z, theta, fl) && theta > 0.0 &&
               theta < 1.0)) {
             // case 1: the Rachford-Rice root left (0,1)
             route_mixture<NC>(r, ob, m, false, kStSaRan, fl, npre, lk, theta);
             return true;
         }
         const double s0 = scale_sum<NC, true>(w0, ix), s1 = scale_sum<NC, true>(w1, iy);
+        double r0[NC], r1[NC];
         Phase<NC> o;
-        phase_eval_sum<NC>(o, e, pp.K, w0, s0, fl, zx);
-        zx = o.Z;
-        double r0[NC];
+        if constexpr (X::kTeam) {
+            X::template eval_pair<NC>(o, e, pp.K, w0, w1, s0, s1, zx, zy, r0, r1, fl);
+        } else {
+            phase_eval_sum<NC>(o, e, pp.K, w0, s0, fl, zx);
+            zx = o.Z;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
-        phase_eval_sum<NC>(o, e, pp.K, w1, s1, fl, zy);
-        zy = o.Z;
+            for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
+            phase_eval_sum<NC>(o, e, pp.K, w1, s1, fl, zy);
+            zy = o.Z;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) lk[i] = r0[i] - o.lnphi[i];
+            for (int i = 0; i < NC; ++i) r1[i] = o.lnphi[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NC; ++i) lk[i] = r0[i] - r1[i];
         fl += NC;
         ++npre;
         if (npre < a.max_pre_ss && ++steps < kStepGuard) return false;
         // triage (Sec. 2.2.3): tpd of the current liquid and vapour
         double tx = 0.0, ty = 0.0, l0[NC], l1[NC];
+        if constexpr (X::kTeam) X::template log_pair<NC>(l0, l1, w0, w1);
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            l0[i] = log(w0[i]);
-            l1[i] = log(w1[i]);
+            if constexpr (!X::kTeam) {
+                l0[i] = log(w0[i]);
+                l1[i] = log(w1[i]);
+            }
             tx += w0[i] * (l0[i] + r0[i] - d[i]);
-            ty += w1[i] * (l1[i] + o.lnphi[i] - d[i]);
+            ty += w1[i] * (l1[i] + r1[i] - d[i]);
         }
         const double dg = (1.0 - theta) * tx + theta * ty;
         fl += 8 * NC + 3;
@@ -627,7 +673,7 @@ struct PreSsItem {
 // SaSs: successive substitution of one stability trial (Sec. 2.2.1, eq.
 // ss_analyser): ln W <- d - ln phi(W)
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct SaSsItem {
     static constexpr int WAVES = 1;   // minimum wavefronts per SIMD
     static constexpr bool kPerMixture = PM;   // one component set per mixture
@@ -732,7 +778,7 @@ struct SaSsItem {
 // SaTr: trust region of one trial in beta = 2 sqrt(W) (Appendix B.1,
 // eqs. tr_sa, analysis_grad, analysis_hess)
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct SaTrItem {
     // two wavefronts per SIMD up to nc = 8: the item holds only ln W across
     // steps (the EOS constants, the feed reference and the last accepted point
@@ -875,8 +921,10 @@ struct SaTrItem {
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             r.lw[t][i] = lw[i];
-            lw[i] = 2.0 * log(sqrt(W[i]) + 0.5 * amax * u[i]);
+            if constexpr (X::kTeam) lw[i] = sqrt(W[i]) + 0.5 * amax * u[i];
+            else lw[i] = 2.0 * log(sqrt(W[i]) + 0.5 * amax * u[i]);
         }
+        if constexpr (X::kTeam) X::template map<NC>(lw, [](double v) { return 2.0 * log(v); });
         fl += 6 * NC;
         facc = tm;
         gacc = gmax;
@@ -950,7 +998,7 @@ struct SaFinItem {
 // ---------------------------------------------------------------------------
 // SpSs: successive substitution of the split (Sec. 2.2.2)
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct SpSsItem {
     static constexpr int WAVES = (NC <= 8 ? 2 : 1);   // minimum wavefronts per SIMD
     static constexpr bool kPerMixture = PM;   // one component set per mixture
@@ -1020,7 +1068,7 @@ struct SpSsItem {
         const Props pp = mix_props<NC, PM>(c.pr, m);
         const FlashArgs &a = c.a;
         double x[NC], y[NC], ix, iy;
-        if (!raw_xy_from_lnk<NC>(x, y, ix, iy, lk, z, theta, fl)) {
+        if (!raw_xy_from_lnk<NC, X>(x, y, ix, iy, lk, z, theta, fl)) {
             if (dem) {
                 // an extrapolated point without a Rachford-Rice root is
                 // rejected like one that does not lower G
@@ -1033,21 +1081,34 @@ struct SpSsItem {
             return true;
         }
         const double s0 = scale_sum<NC, (NC >= 5)>(x, ix), s1 = scale_sum<NC, (NC >= 5)>(y, iy);
+        double r0[NC], r1[NC];
         Phase<NC> o;
-        phase_eval_sum<NC>(o, e, pp.K, x, s0, fl, zx);
-        zx = o.Z;
-        double r0[NC];
+        if constexpr (X::kTeam) {
+            X::template eval_pair<NC>(o, e, pp.K, x, y, s0, s1, zx, zy, r0, r1, fl);
+        } else {
+            phase_eval_sum<NC>(o, e, pp.K, x, s0, fl, zx);
+            zx = o.Z;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
-        phase_eval_sum<NC>(o, e, pp.K, y, s1, fl, zy);
-        zy = o.Z;
+            for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
+            phase_eval_sum<NC>(o, e, pp.K, y, s1, fl, zy);
+            zy = o.Z;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) r1[i] = o.lnphi[i];
+        }
         // G per unit feed (eq. gibbs) where an acceleration check needs it
         const bool dem_next = a.dem_every > 0 && ss + 1 >= 2 && ((ss + 1) % a.dem_every) == 0;
         double G = 0.0;
         if (dem || dem_next) {
+            double lx[NC], ly[NC];
+            if constexpr (X::kTeam) X::template log_pair<NC>(lx, ly, x, y);
 #pragma unroll
-            for (int i = 0; i < NC; ++i)
-                G += (1.0 - theta) * x[i] * (log(x[i]) + r0[i]) + theta * y[i] * (log(y[i]) + o.lnphi[i]);
+            for (int i = 0; i < NC; ++i) {
+                if constexpr (!X::kTeam) {
+                    lx[i] = log(x[i]);
+                    ly[i] = log(y[i]);
+                }
+                G += (1.0 - theta) * x[i] * (lx[i] + r0[i]) + theta * y[i] * (ly[i] + r1[i]);
+            }
             fl += 10 * NC;
         }
         if (dem) {
@@ -1064,7 +1125,7 @@ struct SpSsItem {
         double s[NC], smax = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            s[i] = (r0[i] - o.lnphi[i]) - lk[i];
+            s[i] = (r0[i] - r1[i]) - lk[i];
             smax = fmax(smax, fabs(s[i]));
         }
         fl += 4 * NC;
@@ -1085,7 +1146,7 @@ struct SpSsItem {
         }
         // hand over to the trust region: n^V = theta y from the final K
         MixRec<NC> &r = c.rec[m];
-        if (!xy_from_lnk<NC>(x, y, lk, z, theta, fl)) {
+        if (!xy_from_lnk<NC, X>(x, y, lk, z, theta, fl)) {
             restart_or_fail(c, true, conv ? 0u : kStSplitTr);
             return true;
         }
@@ -1107,7 +1168,7 @@ struct SpSsItem {
 // SpNt: trust region on G over n^V (Appendix B.2, eqs. newton_splitter,
 // split_grad, split_hess), Newton refinement, outputs
 // ---------------------------------------------------------------------------
-template <int NC, bool PM>
+template <int NC, bool PM, class X = Solo>
 struct SpNtItem {
     static constexpr int WAVES = 1;   // minimum wavefronts per SIMD
     static constexpr bool kPerMixture = PM;   // one component set per mixture
@@ -1299,33 +1360,68 @@ struct SpNtItem {
         // scaled Hessian H' = (I - v v' + V((1-th) Phi^V + th Phi^L)V)/(th(1-th)),
         // v_i = sqrt(x_i y_i / z_i), accumulated over the two evaluations
         double vs[NC];
+        if constexpr (X::kTeam) {
 #pragma unroll
-        for (int i = 0; i < NC; ++i) vs[i] = sqrt(w0[i] * w1[i] / z[i]);
+            for (int i = 0; i < NC; ++i) vs[i] = w0[i] * w1[i];
+            X::template map2<NC>(vs, vs, z, [](double p, double q) { return sqrt(p / q); });
+        } else {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) vs[i] = sqrt(w0[i] * w1[i] / z[i]);
+        }
         fl += 4 * NC;
         double F[NP], Hs[NP], dinv[NC];
+        double r0[NC], r1[NC], l0[NC], l1[NC];
+        double Z0;
         Phase<NC> o;
-        phase_eval<NC>(o, e, pp.K, w0, fl, zx);
-        zx = o.Z;
-        phase_derivs<NC>(F, o, e, pp.K, fl);
+        if constexpr (X::kTeam) {
+            // the two phases side by side; then both lanes hold both results
+            double x[NC], y[NC], sv = 0.0, sl = 0.0;
 #pragma unroll
-        for (int i = 0; i < NC; ++i)
+            for (int i = 0; i < NC; ++i) {
+                x[i] = z[i] - v0[i];
+                y[i] = v0[i];
+                sv += y[i];
+                sl += x[i];
+            }
+            const double s0 = scale_sum<NC, true>(x, 1.0 / sl);
+            const double s1 = scale_sum<NC, true>(y, 1.0 / sv);
+            X::template log_pair<NC>(l0, l1, w0, w1);
+            X::template eval_pair<NC>(o, e, pp.K, w0, w1, s0, s1, zx, zy, r0, r1, fl);
+            uint32_t fd = 0;
+            phase_derivs<NC>(F, o, e, pp.K, fd);
+            fl += 2 * fd;
+            X::template sort_pair<NP>(Hs, F);
+            fl += 3 * NP;
+            Z0 = zx;
+        } else {
+            phase_eval<NC>(o, e, pp.K, w0, fl, zx);
+            zx = o.Z;
+            phase_derivs<NC>(F, o, e, pp.K, fl);
 #pragma unroll
-            for (int j = 0; j <= i; ++j) Hs[tri(i, j)] = bvap * vs[i] * vs[j] * F[tri(i, j)];
-        fl += 3 * NP;
-        double r0[NC];
-        const double Z0 = o.Z;
+            for (int i = 0; i < NC; ++i)
 #pragma unroll
-        for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
-        phase_eval<NC>(o, e, pp.K, w1, fl, zy);
-        zy = o.Z;
-        phase_derivs<NC>(F, o, e, pp.K, fl);
+                for (int j = 0; j <= i; ++j) Hs[tri(i, j)] = F[tri(i, j)];   // the liquid phase's
+            fl += 3 * NP;
+            Z0 = o.Z;
+#pragma unroll
+            for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
+            phase_eval<NC>(o, e, pp.K, w1, fl, zy);
+            zy = o.Z;
+            phase_derivs<NC>(F, o, e, pp.K, fl);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) r1[i] = o.lnphi[i];
+        }
         const double th = bvap;
         // gradient of G over n^V (eq. split_grad) and G itself (eq. gibbs)
         double gt[NC], gs[NC], G = 0.0, gmax = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const double fx = log(w0[i]) + r0[i];
-            const double fy = log(w1[i]) + o.lnphi[i];
+            if constexpr (!X::kTeam) {
+                l0[i] = log(w0[i]);
+                l1[i] = log(w1[i]);
+            }
+            const double fx = l0[i] + r0[i];
+            const double fy = l1[i] + r1[i];
             gt[i] = fy - fx;
             G += (z[i] - v0[i]) * fx + v0[i] * fy;
             gmax = fmax(gmax, fabs(gt[i]));
@@ -1366,7 +1462,9 @@ struct SpNtItem {
         for (int i = 0; i < NC; ++i)
 #pragma unroll
             for (int j = 0; j <= i; ++j) {
-                double h = Hs[tri(i, j)] + (1.0 - th) * vs[i] * vs[j] * F[tri(i, j)] - vs[i] * vs[j];
+                const double mx = bvap * vs[i] * vs[j], my = (1.0 - th) * vs[i] * vs[j];
+                double h = fma(-vs[i], vs[j],
+                               fma(mx, Hs[tri(i, j)], my * F[tri(i, j)]));
                 if (i == j) h += 1.0;
                 Hs[tri(i, j)] = h * sc;
             }
@@ -1490,7 +1588,7 @@ struct SpNtItem {
             ++tr;
             return false;
         } while (false);
-        return finish(c, Z0, o.Z, F, fin == 2, vs);
+        return finish(c, Z0, zy, F, fin == 2, vs);
     }
 };
 
