@@ -4,9 +4,11 @@
 // the k gradient.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <vector>
 
 #include "ptflash.h"
 #include "flash_api.hpp"
@@ -92,6 +94,92 @@ static int scratch_address(void **out)
     *out = g_scratch_addr[dev];
     return PTFLASH_OK;
 }
+
+// ---------------------------------------------------------------------------
+// Side streams
+// ---------------------------------------------------------------------------
+
+// Three streams of default priority and the events that order them against the
+// caller's stream.  Held by one call at a time, and only while it enqueues; a
+// call that finds every set taken waits for the launches of the one before it.
+struct SideSet {
+    std::mutex mu;
+    bool made = false, usable = false;
+    hipStream_t st[StreamFork::kMax - 1];
+    hipEvent_t fork, done[StreamFork::kMax - 1];
+};
+constexpr int kSideSets = 4;   // per device
+static SideSet g_side[kMaxDevices][kSideSets];
+static std::atomic<unsigned> g_side_next{0};
+
+static bool make_side_set(SideSet &x)
+{
+    // another thread may be capturing; creating streams here is no part of it
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    bool ok = hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess;
+    for (int k = 0; ok && k < StreamFork::kMax - 1; ++k)
+        ok = hipStreamCreateWithFlags(&x.st[k], hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&x.done[k], hipEventDisableTiming) == hipSuccess;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return ok;
+}
+
+StreamFork::StreamFork(hipStream_t s, int want) : s_(s), set_(nullptr), n_(1)
+{
+    if (want <= 1) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = -1;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+        hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
+        (void)hipGetLastError();
+        return;
+    }
+    // The first free set: a lone caller always gets the set made first, whose
+    // streams and the caller's own fall on different hardware queues (there are
+    // four).  Where every set is taken, wait for one in turn.
+    for (int k = 0; k < kSideSets && !set_; ++k)
+        if (g_side[dev][k].mu.try_lock()) set_ = &g_side[dev][k];
+    if (!set_) {
+        set_ = &g_side[dev][g_side_next.fetch_add(1) % kSideSets];
+        set_->mu.lock();
+    }
+    if (!set_->made) {
+        set_->made = true;
+        set_->usable = make_side_set(*set_);
+        if (!set_->usable) (void)hipGetLastError();
+    }
+    const int want_side = (want < kMax ? want : kMax) - 1;
+    if (set_->usable && hipEventRecord(set_->fork, s_) == hipSuccess)
+        for (int k = 0; k < want_side; ++k, ++n_)
+            if (hipStreamWaitEvent(set_->st[k], set_->fork, 0) != hipSuccess) break;
+    if (n_ == 1) {
+        (void)hipGetLastError();
+        set_->mu.unlock();
+        set_ = nullptr;
+    }
+}
+
+hipStream_t StreamFork::stream(int k) const { return k == 0 ? s_ : set_->st[k - 1]; }
+
+int StreamFork::join()
+{
+    if (!set_) return PTFLASH_OK;
+    int rc = PTFLASH_OK;
+    for (int k = 0; k + 1 < n_; ++k) {
+        if (hipEventRecord(set_->done[k], set_->st[k]) == hipSuccess &&
+            hipStreamWaitEvent(s_, set_->done[k], 0) == hipSuccess)
+            continue;
+        // the caller's memory must not be in use past its own stream's order
+        rc = PTFLASH_EHIP;
+        (void)hipStreamSynchronize(set_->st[k]);
+    }
+    set_->mu.unlock();
+    set_ = nullptr;
+    return rc;
+}
+
+StreamFork::~StreamFork() { (void)join(); }
 
 static void fill_args(FlashArgs &a, const ptflash_problem *p, const ptflash_options *o,
                       const ptflash_result *r)
@@ -392,6 +480,45 @@ static size_t ragged_ws_layout(int64_t n, int form, size_t *flash_off)
     return b + fw;
 }
 
+// One uniform group of a ragged batch, or a chunk of it: mixtures ids[first ..
+// first + cnt) of component count nc.
+struct RaggedJob {
+    int nc;
+    int64_t first, cnt;
+    size_t bytes;    // its buffers and its flash's workspace
+    double cost;     // estimate for the distribution over streams
+};
+
+// Buffers of a job at w (null: only counts); returns the bytes.
+static size_t ragged_buffers(char *w, int64_t cnt, int nc, bool lnk0, bool hint, Uniform &u)
+{
+    size_t used = 0;
+    auto take = [&](size_t bytes) {
+        char *q = w ? w + used : nullptr;
+        used += align256(bytes);
+        return q;
+    };
+    const size_t k = (size_t)cnt, row = k * (size_t)nc * 8;
+    u.z = (double *)take(row);
+    u.Tc = (double *)take(row);
+    u.Pc = (double *)take(row);
+    u.om = (double *)take(row);
+    u.x = (double *)take(row);
+    u.y = (double *)take(row);
+    u.K = (double *)take(row * (size_t)nc);
+    u.T = (double *)take(k * 8);
+    u.P = (double *)take(k * 8);
+    u.beta = (double *)take(k * 8);
+    u.tm = (double *)take(k * 8);
+    u.label = (int8_t *)take(k);
+    u.iters = (int16_t *)take(k * PTFLASH_NITERS * 2);
+    u.status = (uint16_t *)take(k * 2);
+    u.flops = (uint32_t *)take(k * 4);
+    u.lnk0 = lnk0 ? (double *)take(row) : nullptr;
+    u.hint = hint ? (int8_t *)take(k) : nullptr;
+    return used;
+}
+
 static bool problem_ok(const ptflash_problem *p)
 {
     if (!p || p->n < 0) return false;
@@ -412,6 +539,120 @@ static bool options_ok(const ptflash_options *o)
            (o->lanes_split == 0 || o->lanes_split == 1 || o->lanes_split == 16 ||
             o->lanes_split == 32) &&
            (o->lanes_ss == 0 || o->lanes_ss == 1 || o->lanes_ss == 16 || o->lanes_ss == 32);
+}
+
+static int flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *o,
+                        ptflash_result *r, void *ws, size_t ws_bytes, hipStream_t s)
+{
+    if (!p || p->n < 0 || !options_ok(o) || !r) return PTFLASH_EINVAL;
+    if (p->n == 0) return PTFLASH_OK;
+    if (p->n > (int64_t)1 << 30) return PTFLASH_EUNSUPPORTED;
+    if (!p->nc_of || !p->off || !p->koff || !p->z || !p->T || !p->P || !p->Tc || !p->Pc ||
+        !p->omega || !p->kij)
+        return PTFLASH_EINVAL;
+    if (!r->label || !r->beta || !r->x || !r->y) return PTFLASH_EINVAL;
+    if (o->keep_factor || r->factor) return PTFLASH_EINVAL;
+    size_t foff = 0;
+    const size_t need = ragged_ws_layout(p->n, o->form, &foff);
+    if (!ws || need == 0 || ws_bytes < need) return PTFLASH_EWORKSPACE;
+    if (((uintptr_t)ws & 255u) != 0) return PTFLASH_EINVAL;
+    const int64_t n = p->n, ch = ragged_chunk(n, o->form);
+    char *w = (char *)ws;
+    unsigned long long *counts = (unsigned long long *)w;
+    unsigned long long *cursor = counts + kBuckets;
+    w += align256(2 * kBuckets * sizeof(unsigned long long));
+    uint32_t *ids = (uint32_t *)w;
+    w += align256((size_t)n * 4);
+    char *const arena = w;   // the groups' buffers and workspaces
+    const size_t arena_bytes = need - (size_t)(arena - (char *)ws);
+
+    // group sizes (one host synchronisation)
+    hipLaunchKernelGGL(zero_u64, dim3(1), dim3(64), 0, s, counts, 2 * kBuckets);
+    const int64_t blocks = (n + kBlock - 1) / kBlock;
+    const unsigned cgrid = (unsigned)(blocks < 4096 ? blocks : 4096);
+    hipLaunchKernelGGL(ragged_count, dim3(cgrid), dim3(kBlock), 0, s, n, p->nc_of, p->off,
+                       counts);
+    unsigned long long hc[kBuckets];
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return PTFLASH_EHIP;
+    BucketStarts st;
+    int64_t acc = 0;
+    for (int b = 0; b < kBuckets; ++b) { st.s[b] = acc; acc += (int64_t)hc[b]; }
+    hipLaunchKernelGGL(ragged_sort, dim3((unsigned)blocks), dim3(kBlock), 0, s, n, p->nc_of,
+                       p->off, st, cursor, ids);
+    ptflash_result rr = *r;
+    if (hc[0] > 0)
+        hipLaunchKernelGGL(ragged_invalid, dim3((unsigned)((hc[0] + kBlock - 1) / kBlock)),
+                           dim3(kBlock), 0, s, (int64_t)hc[0], ids, p->off, p->z, rr);
+    if (hipGetLastError() != hipSuccess) return PTFLASH_EHIP;
+    const bool r_tm = r->tm != nullptr;
+    const RaggedIn in{p->off, p->koff, p->z, p->T, p->P, p->Tc, p->Pc, p->omega, p->kij,
+                      p->lnk0, p->hint};
+    std::vector<RaggedJob> jobs;
+    for (int nc = kMaxNc; nc >= kMinNc; --nc)
+        for (int64_t c0 = 0; c0 < (int64_t)hc[nc]; c0 += ch) {
+            const int64_t cnt = ((int64_t)hc[nc] - c0) < ch ? ((int64_t)hc[nc] - c0) : ch;
+            Uniform u;
+            size_t fw = 0;
+            if (Dispatch<WsF>::run(nc, cnt, o->form, &fw) != PTFLASH_OK)
+                return PTFLASH_EUNSUPPORTED;
+            const size_t bytes = ragged_buffers(nullptr, cnt, nc, p->lnk0 != nullptr,
+                                                p->hint != nullptr, u) + fw;
+            if (bytes > arena_bytes) return PTFLASH_EWORKSPACE;
+            jobs.push_back(RaggedJob{nc, st.s[nc] + c0, cnt, bytes,
+                                     (double)(nc * nc) * (double)(cnt + 50000)});
+        }
+    // The groups are independent, and each is a chain of stages whose tails
+    // leave most of the device idle, so they run on several streams: as many
+    // groups at a time as the workspace holds side by side, the largest first,
+    // each on the stream with the least work so far.  (The plain form waits
+    // for the device inside the call and keeps to the caller's stream.)
+    // 500,000 mixtures of seven component counts: 16.3 ms one after another, 10.0 ms
+    // this way.
+    std::vector<char> done(jobs.size(), 0);
+    for (size_t left = jobs.size(); left > 0;) {
+        std::vector<size_t> round;
+        std::vector<char *> at;
+        size_t used = 0;
+        for (size_t k = 0; k < jobs.size(); ++k)
+            if (!done[k] && used + jobs[k].bytes <= arena_bytes) {
+                done[k] = 1;
+                round.push_back(k);
+                at.push_back(arena + used);
+                used += jobs[k].bytes;
+            }
+        left -= round.size();
+        StreamFork f(s, o->form == PTFLASH_FORM_PLAIN ? 1 : (int)round.size());
+        double load[StreamFork::kMax] = {};
+        for (size_t r = 0; r < round.size(); ++r) {
+            const RaggedJob &j = jobs[round[r]];
+            int q = 0;
+            for (int k = 1; k < f.count(); ++k)
+                if (load[k] < load[q]) q = k;
+            load[q] += j.cost;
+            const hipStream_t sj = f.stream(q);
+            Uniform u;
+            const size_t fo = ragged_buffers(at[r], j.cnt, j.nc, p->lnk0 != nullptr,
+                                             p->hint != nullptr, u);
+            const uint32_t *cid = ids + j.first;
+            RaggedMove<kMinNc>::run(j.nc, true, j.cnt, cid, in, u, p->off, rr, sj);
+            ptflash_problem sub{j.cnt, j.nc, 1, u.z, u.T, u.P, u.Tc, u.Pc, u.om, u.K, u.lnk0,
+                                u.hint};
+            ptflash_result sr{u.label, u.beta, u.x, u.y, u.iters, u.status, u.flops, nullptr,
+                              r_tm ? u.tm : nullptr};
+            FlashArgs a;
+            fill_args(a, &sub, o, &sr);
+            const int rc = Dispatch<FlashF>::run(j.nc, a, &sub, o, at[r] + fo, sj);
+            if (rc) return rc;   // f joins what has been enqueued
+            RaggedMove<kMinNc>::run(j.nc, false, j.cnt, cid, in, u, p->off, rr, sj);
+            if (hipGetLastError() != hipSuccess) return PTFLASH_EHIP;
+        }
+        const int rc = f.join();
+        if (rc) return rc;
+    }
+    return PTFLASH_OK;
 }
 
 }  // namespace ptf
@@ -578,89 +819,11 @@ size_t ptflash_ragged_workspace_bytes(const ptflash_ragged_problem *p,
 int ptflash_flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *o,
                          ptflash_result *r, void *ws, size_t ws_bytes, hipStream_t s)
 {
-    if (!p || p->n < 0 || !options_ok(o) || !r) return PTFLASH_EINVAL;
-    if (p->n == 0) return PTFLASH_OK;
-    if (p->n > (int64_t)1 << 30) return PTFLASH_EUNSUPPORTED;
-    if (!p->nc_of || !p->off || !p->koff || !p->z || !p->T || !p->P || !p->Tc || !p->Pc ||
-        !p->omega || !p->kij)
-        return PTFLASH_EINVAL;
-    if (!r->label || !r->beta || !r->x || !r->y) return PTFLASH_EINVAL;
-    if (o->keep_factor || r->factor) return PTFLASH_EINVAL;
-    size_t foff = 0;
-    const size_t need = ragged_ws_layout(p->n, o->form, &foff);
-    if (!ws || need == 0 || ws_bytes < need) return PTFLASH_EWORKSPACE;
-    if (((uintptr_t)ws & 255u) != 0) return PTFLASH_EINVAL;
-    const int64_t n = p->n, ch = ragged_chunk(n, o->form), C = kMaxNc;
-    char *w = (char *)ws;
-    unsigned long long *counts = (unsigned long long *)w;
-    unsigned long long *cursor = counts + kBuckets;
-    w += align256(2 * kBuckets * sizeof(unsigned long long));
-    uint32_t *ids = (uint32_t *)w;
-    w += align256((size_t)n * 4);
-    Uniform u;
-    auto takeb = [&](size_t bytes) { char *q = w; w += align256(bytes); return q; };
-    u.z = (double *)takeb(ch * C * 8);
-    u.Tc = (double *)takeb(ch * C * 8);
-    u.Pc = (double *)takeb(ch * C * 8);
-    u.om = (double *)takeb(ch * C * 8);
-    u.x = (double *)takeb(ch * C * 8);
-    u.y = (double *)takeb(ch * C * 8);
-    u.K = (double *)takeb(ch * C * C * 8);
-    u.T = (double *)takeb(ch * 8);
-    u.P = (double *)takeb(ch * 8);
-    u.beta = (double *)takeb(ch * 8);
-    u.label = (int8_t *)takeb(ch);
-    u.iters = (int16_t *)takeb(ch * PTFLASH_NITERS * 2);
-    u.status = (uint16_t *)takeb(ch * 2);
-    u.flops = (uint32_t *)takeb(ch * 4);
-    u.tm = (double *)takeb(ch * 8);
-    u.lnk0 = (double *)takeb(ch * C * 8);
-    u.hint = (int8_t *)takeb(ch);
-    void *fws = (char *)ws + foff;
-    const size_t fws_bytes = ws_bytes - foff;
-
-    // group sizes (one host synchronisation)
-    hipLaunchKernelGGL(zero_u64, dim3(1), dim3(64), 0, s, counts, 2 * kBuckets);
-    const int64_t blocks = (n + kBlock - 1) / kBlock;
-    const unsigned cgrid = (unsigned)(blocks < 4096 ? blocks : 4096);
-    hipLaunchKernelGGL(ragged_count, dim3(cgrid), dim3(kBlock), 0, s, n, p->nc_of, p->off,
-                       counts);
-    unsigned long long hc[kBuckets];
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    try {
+        return flash_ragged(p, o, r, ws, ws_bytes, s);
+    } catch (...) {   // host memory for the list of groups, or a mutex
         return PTFLASH_EHIP;
-    BucketStarts st;
-    int64_t acc = 0;
-    for (int b = 0; b < kBuckets; ++b) { st.s[b] = acc; acc += (int64_t)hc[b]; }
-    hipLaunchKernelGGL(ragged_sort, dim3((unsigned)blocks), dim3(kBlock), 0, s, n, p->nc_of,
-                       p->off, st, cursor, ids);
-    ptflash_result rr = *r;
-    if (hc[0] > 0)
-        hipLaunchKernelGGL(ragged_invalid, dim3((unsigned)((hc[0] + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, (int64_t)hc[0], ids, p->off, p->z, rr);
-    if (hipGetLastError() != hipSuccess) return PTFLASH_EHIP;
-    const RaggedIn in{p->off, p->koff, p->z, p->T, p->P, p->Tc, p->Pc, p->omega, p->kij,
-                      p->lnk0, p->hint};
-    for (int nc = kMinNc; nc <= kMaxNc; ++nc) {
-        for (int64_t c0 = 0; c0 < (int64_t)hc[nc]; c0 += ch) {
-            const int64_t cnt = ((int64_t)hc[nc] - c0) < ch ? ((int64_t)hc[nc] - c0) : ch;
-            const uint32_t *cid = ids + st.s[nc] + c0;
-            RaggedMove<kMinNc>::run(nc, true, cnt, cid, in, u, p->off, rr, s);
-            ptflash_problem sub{cnt, nc, 1, u.z, u.T, u.P, u.Tc, u.Pc, u.om, u.K,
-                                p->lnk0 ? u.lnk0 : nullptr, p->hint ? u.hint : nullptr};
-            ptflash_result sr{u.label, u.beta, u.x, u.y, u.iters, u.status, u.flops, nullptr,
-                              r->tm ? u.tm : nullptr};
-            if (fws_bytes < ptflash_workspace_bytes(&sub, o)) return PTFLASH_EWORKSPACE;
-            FlashArgs a;
-            fill_args(a, &sub, o, &sr);
-            int rc = Dispatch<FlashF>::run(nc, a, &sub, o, fws, s);
-            if (rc) return rc;
-            RaggedMove<kMinNc>::run(nc, false, cnt, cid, in, u, p->off, rr, s);
-            if (hipGetLastError() != hipSuccess) return PTFLASH_EHIP;
-        }
     }
-    return PTFLASH_OK;
 }
 
 int ptflash_flash_noalloc(const ptflash_problem *p, const ptflash_options *o,
