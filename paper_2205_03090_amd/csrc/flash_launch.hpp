@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "flash_api.hpp"
@@ -225,14 +226,92 @@ __device__ __forceinline__ void append_slot(const Lists &L, int list, int l, uin
     }
 }
 
+// The last items of a persistent stage's wavefront, each finished by a team of
+// lanes (flash_team.hpp), which needs about half the instructions for a step.
+// The items pass through LDS in their state between two steps.  The team's loop
+// is a function of its own: inlined, its registers made the stage's loop spill
+// (544 bytes a lane instead of 144 at nc 8) and cost more than the teams gain.
+// Its arguments stay in the kernel's argument segment, where the compiler knows
+// them to be the same in all lanes.
+using TailTeam = Team<8, kBlock / 64>;
+
+// Component counts whose split trust region ends that way.  Measured on whole
+// flashes (us, without / with teams; shared sets unless noted): nc 2
+// 1533 / 1382 at 500,000 mixtures, nc 3 2282 / 2200 at 1,000,000, nc 5 1998 / 1860 and
+// (own sets) 2306 / 2074 at 500,000, nc 7 3487 / 3209 at 1,000,000, nc 8 1893 / 1679 at
+// 200,000, 3830 / 3565 at 1,000,000, and 2420 / 2230 for 500,000 warm starts.  At
+// nc 4 the stage alone just fits the registers of two wavefronts per SIMD, and
+// with the call it spills (3970 / 4510 at 2,000,000; 4024 with one wavefront); from
+// nc 10 on the teams spill as the stage does (2890 / 3015 for a flash and its
+// gradient of 300,000 at nc 10).
+template <int NC>
+constexpr bool team_tail_ok()
+{
+    return NC <= 8 && NC != 4;
+}
+
+template <int NC>
+struct StageArgs {   // the leading arguments of stage_persistent, as laid out in the segment
+    Ctx<NC> c;
+    const double *Tc, *Pc, *om, *K;
+};
+
+template <class Item>
+constexpr int item_words()
+{
+    return (int)((sizeof(Item) + 7) / 8);
+}
+
+template <class TeamItem, int NC>
+__device__ __noinline__ void team_tail(uint64_t segment,
+                                       const __attribute__((address_space(3))) double *state,
+                                       int count)
+{
+    constexpr int W = item_words<TeamItem>(), A = (int)(sizeof(StageArgs<NC>) / 8);
+    static_assert(sizeof(StageArgs<NC>) % 8 == 0, "copied by words");
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)segment);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(segment >> 32));
+    const auto *seg = (const __attribute__((address_space(4))) uint64_t *)(lo | (hi << 32));
+    uint64_t words[A];
+#pragma unroll
+    for (int k = 0; k < A; ++k) words[k] = seg[k];
+    StageArgs<NC> a;
+    __builtin_memcpy((void *)&a, words, sizeof(a));
+    a.c.pr = Props{a.Tc, a.Pc, a.om, a.K};
+    const int team = (int)__lane_id() / TailTeam::kLanes;
+    bool live = team < count;   // the same in every lane of a team
+    double w[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) w[k] = state[(live ? team : 0) * W + k];
+    TeamItem it;
+    __builtin_memcpy((void *)&it, w, sizeof(it));
+    while (__ballot(live) != 0ull) {
+        if (live) live = !it.step(a.c);
+    }
+}
+
+// Wavefronts per SIMD that a persistent stage's registers are to allow.  The small
+// component counts reach two by themselves, but not around a call.
+template <class Item, int NC, class TeamItem>
+constexpr int stage_waves()
+{
+    return !std::is_void_v<TeamItem> && NC <= 3 && Item::WAVES < 2 ? 2 : Item::WAVES;
+}
+
 // Persistent stage: one item per lane; lanes whose item finished take the
 // next input positions of the wavefront (Claim).  The
 // list entries the steps produce are staged per wavefront in LDS and
 // appended kStage at a time (one atomic per batch).  Every item finishes
 // within its stage's iteration caps (and kStepGuard steps), so every
 // wavefront reaches the exit, where it appends what it still holds.
-template <class Item, int NC>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Item::WAVES)))
+//
+// TeamItem: void, or the team's form of the item (team_tail).  An item whose step
+// count is far above the average keeps its wavefront, with a lane or two live,
+// long after the input has run dry.  So once it is dry and no more items are left
+// than the wavefront has teams, the teams finish them.
+template <class Item, int NC, class TeamItem>
+__global__ void __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(stage_waves<Item, NC, TeamItem>())))
 stage_persistent(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__ Pc,
                  const double *__restrict__ om, const double *__restrict__ K,
                  unsigned long long *__restrict__ take)
@@ -263,6 +342,28 @@ stage_persistent(Ctx<NC> c, const double *__restrict__ Tc, const double *__restr
             }
         }
         if (__ballot(!gone) == 0ull) break;
+        if constexpr (!std::is_void_v<TeamItem>) {
+            static_assert(sizeof(TeamItem) == sizeof(Item) && OUT == 0u,
+                          "the two forms share their state and list nothing");
+            const unsigned long long left = __ballot(live);
+            if (__ballot(gone) != 0ull && __popcll(left) <= TailTeam::kPerWave) {
+                constexpr int W = item_words<Item>();
+                __shared__ double state[kWavesPerBlock][TailTeam::kPerWave * W];
+                double *q = state[threadIdx.x / 64];
+                if (live) {
+                    double w[W];
+                    __builtin_memcpy(w, (const void *)&it, sizeof(Item));
+                    const int r = (int)__popcll(left & lanes_below(lane)) * W;
+#pragma unroll
+                    for (int k = 0; k < W; ++k) q[r + k] = w[k];
+                }
+                wave_lds_sync();
+                team_tail<TeamItem, NC>(
+                    (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(),
+                    (const __attribute__((address_space(3))) double *)q, (int)__popcll(left));
+                break;
+            }
+        }
         it.ob.clear();
         if (live) live = !it.step(c);
 #pragma unroll
@@ -778,16 +879,17 @@ int grid_for(const void *kernel, int block, int requested, int64_t n, int lanes_
     return (int)(need < 1 ? 1 : need < full ? need : full);
 }
 
-template <class Item, int NC>
+template <class Item, int NC, class TeamItem = void>
 int run_persistent_stage(const Ctx<NC> &c, const ptflash_problem *p,
                                 const ptflash_options *o, int take_slot, hipStream_t s)
 {
     const int block = o->block > 0 ? o->block : tuned_block(NC, Item::kPerMixture);
     if (block % 64 != 0 || block > kBlock) return PTFLASH_EINVAL;
-    const int grid = grid_for((const void *)stage_persistent<Item, NC>, block, o->grid, p->n, 1);
+    const int grid =
+        grid_for((const void *)stage_persistent<Item, NC, TeamItem>, block, o->grid, p->n, 1);
     if (grid <= 0) return PTFLASH_EHIP;
-    hipLaunchKernelGGL((stage_persistent<Item, NC>), dim3(grid), dim3(block), 0, s, c, p->Tc,
-                       p->Pc, p->omega, p->kij, c.L.cnt(take_slot));
+    hipLaunchKernelGGL((stage_persistent<Item, NC, TeamItem>), dim3(grid), dim3(block), 0, s, c,
+                       p->Tc, p->Pc, p->omega, p->kij, c.L.cnt(take_slot));
     return hipGetLastError() == hipSuccess ? PTFLASH_OK : PTFLASH_EHIP;
 }
 
@@ -899,8 +1001,12 @@ int launch_persistent(const FlashArgs &a, const ptflash_problem *p, const ptflas
     if ((rc = run_persistent_stage<SaFinItem<NC, PM>, NC>(c, p, o, kTake0 + 4, s))) return rc;
     if (a.stability_only) return PTFLASH_OK;
     if ((rc = run_tr_stage<SpSsSolo, SpSsGroup, NC, PM>(c, p, o, lss, kTake0 + 5, s))) return rc;
-    if ((rc = run_tr_stage<SpNtSolo, SpNtGroup, NC, PM>(c, p, o, lsp, kTake0 + 6, s))) return rc;
-    return PTFLASH_OK;
+    if constexpr (team_tail_ok<NC>()) {
+        if (lsp == 1)
+            return run_persistent_stage<SpNtItem<NC, PM>, NC, SpNtItem<NC, PM, TailTeam>>(
+                c, p, o, kTake0 + 6, s);
+    }
+    return run_tr_stage<SpNtSolo, SpNtGroup, NC, PM>(c, p, o, lsp, kTake0 + 6, s);
 }
 
 // Reads a device counter after the work queued so far (host sync).

@@ -22,7 +22,8 @@ namespace ptf {
 
 // A team: D lanes per parity, 2 D lanes per mixture, 32 / D mixtures per
 // wavefront.  Lane l of the wavefront: parity l & 1, member (l >> 1) % D.
-template <int D>
+// WAVES: wavefronts of the block, at most.
+template <int D, int WAVES = 1>
 struct Team {
     static constexpr bool kTeam = true;
     static constexpr int kLanes = 2 * D;
@@ -31,11 +32,10 @@ struct Team {
     static __device__ __forceinline__ int member() { return ((int)threadIdx.x >> 1) % D; }
     static __device__ __forceinline__ bool odd() { return (threadIdx.x & 1u) != 0u; }
 
-    // The members' exchange buffer of this parity's half of the team (blocks
-    // are one wavefront).
+    // The members' exchange buffer of this parity's half of the team.
     static __device__ __forceinline__ double *buf()
     {
-        __shared__ double b[2 * kPerWave * 2 * kMaxNc];
+        __shared__ double b[WAVES * 2 * kPerWave * 2 * kMaxNc];
         const int half = 2 * ((int)threadIdx.x / kLanes) + ((int)threadIdx.x & 1);
         return b + half * 2 * kMaxNc;
     }
