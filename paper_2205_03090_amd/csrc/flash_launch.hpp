@@ -33,6 +33,10 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Largest component count with teams (flash_team.hpp): above it a lane's
+// matrices spill in either form and a team gains nothing reliably.
+constexpr int kTeamMaxNc = 12;
+
 // Zeroes n counters of a counter block (kCounterStride apart).
 __global__ void reset_counters(unsigned long long *q, int n)
 {
@@ -290,6 +294,30 @@ __device__ __noinline__ void team_tail(uint64_t segment,
     }
 }
 
+// Gives the wavefront's live items (left: their lanes, at most one per team)
+// to its teams and returns when they are done.  Called by all 64 lanes.
+template <class TeamItem, int NC, class Item>
+__device__ __forceinline__ void finish_by_teams(const Item &it, bool live,
+                                                unsigned long long left, int lane)
+{
+    static_assert(sizeof(TeamItem) == sizeof(Item) && Item::OUT == 0u,
+                  "the two forms share their state and list nothing");
+    constexpr int W = item_words<Item>();
+    __shared__ double state[kWavesPerBlock][TailTeam::kPerWave * W];
+    double *q = state[threadIdx.x / 64];
+    if (live) {
+        double w[W];
+        __builtin_memcpy(w, (const void *)&it, sizeof(Item));
+        const int r = (int)__popcll(left & lanes_below(lane)) * W;
+#pragma unroll
+        for (int k = 0; k < W; ++k) q[r + k] = w[k];
+    }
+    wave_lds_sync();
+    team_tail<TeamItem, NC>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(),
+                                 (const __attribute__((address_space(3))) double *)q,
+                                 (int)__popcll(left));
+}
+
 // Wavefronts per SIMD that a persistent stage's registers are to allow.  The small
 // component counts reach two by themselves, but not around a call.
 template <class Item, int NC, class TeamItem>
@@ -343,24 +371,9 @@ stage_persistent(Ctx<NC> c, const double *__restrict__ Tc, const double *__restr
         }
         if (__ballot(!gone) == 0ull) break;
         if constexpr (!std::is_void_v<TeamItem>) {
-            static_assert(sizeof(TeamItem) == sizeof(Item) && OUT == 0u,
-                          "the two forms share their state and list nothing");
             const unsigned long long left = __ballot(live);
             if (__ballot(gone) != 0ull && __popcll(left) <= TailTeam::kPerWave) {
-                constexpr int W = item_words<Item>();
-                __shared__ double state[kWavesPerBlock][TailTeam::kPerWave * W];
-                double *q = state[threadIdx.x / 64];
-                if (live) {
-                    double w[W];
-                    __builtin_memcpy(w, (const void *)&it, sizeof(Item));
-                    const int r = (int)__popcll(left & lanes_below(lane)) * W;
-#pragma unroll
-                    for (int k = 0; k < W; ++k) q[r + k] = w[k];
-                }
-                wave_lds_sync();
-                team_tail<TeamItem, NC>(
-                    (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(),
-                    (const __attribute__((address_space(3))) double *)q, (int)__popcll(left));
+                finish_by_teams<TeamItem, NC>(it, live, left, lane);
                 break;
             }
         }
@@ -490,8 +503,52 @@ __device__ __forceinline__ void fused_item(const Ctx<NC> &c, uint32_t id, Outbox
     }
 }
 
-template <int NC, bool PM>
+// Component counts whose fused form ends the split trust region with teams: all
+// whose teams keep their matrices in registers, or nearly.  Measured (us, without /
+// with teams, lane pairs; shared sets unless noted): nc 3 401 / 374 at 40,000 mixtures,
+// 720 / 660 at 150,000, nc 5 775 / 655 at 60,000, 1486 / 1305 at 150,000, nc 8 830 / 555 at
+// 25,000, 1190 / 810 at 60,000, 1470 / 1225 at 100,000, nc 10 1380 / 1046 at 60,000, nc 12 (own
+// sets) 3140 / 2306 at 60,000; but nc 16 6715 / 7540 and nc 20 10,810 / 12,280 at 40,000.
+template <int NC>
+constexpr bool fused_tail_ok()
+{
+    return NC <= kTeamMaxNc;
+}
+
+// Wavefronts per SIMD that the fused form's registers are to allow: up to nc 4 it
+// reached two by itself, but does not around a call.
+template <int NC>
+constexpr int fused_waves()
+{
+    return NC <= 4 ? 2 : 1;
+}
+
+// As fused_item, for all lanes of the wavefront together (run: this lane has an
+// item), with the last items finished by teams.
+template <class Item, class TeamItem, int NC>
+__device__ __forceinline__ void fused_item_tail(const Ctx<NC> &c, uint32_t id, bool run)
+{
+    const int lane = (int)__lane_id();
+    Item it;
+    bool live = false;
+    if (run) live = it.begin(c, id);
+    for (;;) {
+        const unsigned long long left = __ballot(live);
+        if (left == 0ull) return;
+        if (__popcll(left) <= TailTeam::kPerWave) {
+            finish_by_teams<TeamItem, NC>(it, live, left, lane);
+            return;
+        }
+        it.ob.clear();
+        if (live) live = !it.step(c);
+    }
+}
+
+// TAIL: the split trust region, whose longest mixture keeps the other 31 of a
+// wavefront waiting for 20 steps and more, ends with teams (team_tail).
+template <int NC, bool PM, bool TAIL>
 __global__ void __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(fused_waves<NC>())))
 stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__ Pc,
             const double *__restrict__ om, const double *__restrict__ K)
 {
@@ -499,11 +556,11 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     // the two lanes of a pair are neighbours in one wavefront
     const int64_t m = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 1;
     const uint32_t t = threadIdx.x & 1u;
-    if (m >= c.a.n) return;   // both lanes of the pair
+    const bool in = m < c.a.n;   // both lanes of the pair
     const uint32_t id = (uint32_t)m;
     Outbox o;
     o.clear();
-    if (t == 0) {
+    if (in && t == 0) {
         fused_item<FeedItem<NC, PM>, NC>(c, id, o);
         if (o.l0 == L_PRE) fused_item<PreSsItem<NC, PM>, NC>(c, id, o);
     }
@@ -518,11 +575,16 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         if (t == 0) fused_item<SaFinItem<NC, PM>, NC>(c, id, o);
     }
-    if (t != 0 || c.a.stability_only) return;
-    if (o.l0 == L_SPLIT) {
+    if (c.a.stability_only) return;
+    bool nt = false;
+    if (t == 0 && o.l0 == L_SPLIT) {
         fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
-        if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
+        nt = o.l0 == L_NT || o.l0 == L_NTP;
     }
+    if constexpr (TAIL)
+        fused_item_tail<SpNtItem<NC, PM>, SpNtItem<NC, PM, TailTeam>, NC>(c, id, nt);
+    else if (nt)
+        fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
 }
 
 // The fused form with a team of lanes per mixture (flash_team.hpp): as
@@ -1067,7 +1129,7 @@ int launch_fused(const FlashArgs &a, const ptflash_problem *p, const ptflash_opt
     setup_ctx<NC>(c, a, p->n, ws, &tail);
     const int64_t blocks = (2 * p->n + block - 1) / block;   // two lanes per mixture
     if (blocks > 0)
-        hipLaunchKernelGGL((stage_fused<NC, PM>), dim3((unsigned)blocks), dim3(block), 0, s, c,
+        hipLaunchKernelGGL((stage_fused<NC, PM, fused_tail_ok<NC>()>), dim3((unsigned)blocks), dim3(block), 0, s, c,
                            p->Tc, p->Pc, p->omega, p->kij);
     return hipGetLastError() == hipSuccess ? PTFLASH_OK : PTFLASH_EHIP;
 }
@@ -1075,16 +1137,15 @@ int launch_fused(const FlashArgs &a, const ptflash_problem *p, const ptflash_opt
 // Batches up to this many mixtures run the fused form with a team of lanes per
 // mixture (0: never).  A team takes 8 or 16 lanes where the lane pair takes two
 // and needs about half the instructions per step, so it wins while the device has
-// lanes to spare.  Measured (MI355X, us per call, lane pair against team): nc 3
-// 295 / 196 at 1000 mixtures, 336 / 258 at 12,000, 300 / 304 at 24,000, 399 / 603 at
-// 60,000; nc 8 503 / 262 at 1000, 753 / 630 at 12,000, 742 / 648 at 16,000, 806 / 811
-// at 24,000; nc 5 452 / 260, 511 / 466 at 12,000, 556 / 636 at 16,000; nc 12 (own
-// sets) 1574 / 1005, 1562 / 1509 at 12,000.  Above nc 12 a lane's matrices spill in
-// either form and the team gains nothing reliably.
+// lanes to spare.  Measured (MI355X, us per call, team against lane pairs): nc 3
+// 168 / 247 at 2000 mixtures, 248 / 314 at 16,000, 305 / 272 at 24,000; nc 4 352 / 351 at
+// 20,000; nc 5 254 / 383 at 4000, 378 / 393 at 8000, 473 / 433 at 12,000; nc 8 269 / 463 at
+// 1000, 481 / 557 at 10,000, 620 / 629 at 12,000; nc 10 607 / 650 at 10,000; nc 12 (own sets)
+// 893 / 1186 at 4000, 1247 / 1452 at 10,000, 1510 / 1203 at 12,000.
 template <int NC>
 constexpr int64_t team_max_n()
 {
-    return NC <= 4 ? 24000 : NC <= 12 ? 12000 : 0;
+    return NC <= 4 ? 20000 : NC <= kTeamMaxNc ? 10000 : 0;
 }
 
 template <int NC, bool PM>
@@ -1148,13 +1209,19 @@ size_t nc_workspace_bytes(int64_t n, int form)
 // launch unless the caller sets its launch shape (grid, block or lanes per
 // mixture): below it the staged form's time is the sum of its stages'
 // slowest items, which the fused form's slowest whole path undercuts.  The
-// fused form keeps a whole mixture on one lane pair, so from nc ~ 12, where
-// the staged form moves the trust-region work onto lane groups, it pays off
-// only for smaller batches (gfx950, measured at nc 3, 5, 8, 12, 16 and 20).
+// fused form keeps a whole mixture on one lane pair, so above nc 12, where
+// the staged form moves the trust-region work onto lane groups and the fused
+// form's tail has no teams, it pays off only for smaller batches.  Measured
+// (MI355X, us, staged / fused): nc 2 1223 / 1073 at 300,000, 1324 / 1403 at 400,000; nc 4
+// 1200 / 991 at 200,000, 1350 / 1372 at 300,000 (own sets 1671 / 1347); nc 5 1418 / 1312 at
+// 150,000, 1518 / 1709 at 200,000; nc 8 1448 / 1034 at 80,000, 1917 / 1596 at 150,000,
+// 1703 / 2056 at 200,000; nc 9 1644 / 1487 at 100,000, 1746 / 1775 at 130,000; nc 12 2682 / 2398
+// at 60,000, 2695 / 2676 at 80,000 (own sets 2893 / 3105).
 template <int NC>
 constexpr int64_t fused_max_n()
 {
-    return NC <= 8 ? 150000 : 400000 / NC;
+    return NC <= 4 ? 300000 : NC <= 8 ? 150000 : NC <= 10 ? 120000 : NC <= 12 ? 70000
+                                                                           : 400000 / NC;
 }
 
 template <int NC, bool PM>
