@@ -313,6 +313,8 @@ __device__ __forceinline__ void finish_by_teams(const Item &it, bool live,
         for (int k = 0; k < W; ++k) q[r + k] = w[k];
     }
     wave_lds_sync();
+    // the item's lane has written its record, the team's lanes read it
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     team_tail<TeamItem, NC>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(),
                                  (const __attribute__((address_space(3))) double *)q,
                                  (int)__popcll(left));
@@ -556,7 +558,9 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     // the two lanes of a pair are neighbours in one wavefront
     const int64_t m = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 1;
     const uint32_t t = threadIdx.x & 1u;
+    // with teams at the end, a wavefront's lanes stay together
     const bool in = m < c.a.n;   // both lanes of the pair
+    if (!TAIL && !in) return;
     const uint32_t id = (uint32_t)m;
     Outbox o;
     o.clear();
@@ -576,15 +580,18 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
         if (t == 0) fused_item<SaFinItem<NC, PM>, NC>(c, id, o);
     }
     if (c.a.stability_only) return;
-    bool nt = false;
-    if (t == 0 && o.l0 == L_SPLIT) {
-        fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
-        nt = o.l0 == L_NT || o.l0 == L_NTP;
-    }
-    if constexpr (TAIL)
+    if constexpr (TAIL) {
+        bool nt = false;
+        if (t == 0 && o.l0 == L_SPLIT) {
+            fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
+            nt = o.l0 == L_NT || o.l0 == L_NTP;
+        }
         fused_item_tail<SpNtItem<NC, PM>, SpNtItem<NC, PM, TailTeam>, NC>(c, id, nt);
-    else if (nt)
-        fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
+    } else {
+        if (t != 0 || o.l0 != L_SPLIT) return;
+        fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
+        if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
+    }
 }
 
 // The fused form with a team of lanes per mixture (flash_team.hpp): as
