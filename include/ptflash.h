@@ -84,11 +84,12 @@ extern "C" {
 #define PTFLASH_FORM_PERSISTENT 0 /* one launch per stage; waves refill finished
                                      lanes.  With grid, block and the lanes
                                      options all 0, a batch of n mixtures runs
-                                     as FUSED when n <= 150000 (nc <= 8) or
-                                     n * nc <= 400000 (nc > 8), the smallest
-                                     of these with a team of lanes per mixture
-                                     (n <= 24000 at nc <= 4, n <= 12000 up to
-                                     nc = 12)                             */
+                                     as FUSED when n <= 300000 (nc <= 4),
+                                     150000 (nc <= 8), 120000 (nc <= 10),
+                                     70000 (nc <= 12) or n * nc <= 400000
+                                     (above), the smallest of these with a
+                                     team of lanes per mixture (n <= 20000 at
+                                     nc <= 4, n <= 10000 up to nc = 12)   */
 #define PTFLASH_FORM_PLAIN 1      /* one launch per stage iteration + compaction */
 #define PTFLASH_FORM_FUSED 2      /* one launch; a lane pair carries one mixture
                                      through every stage, its two stability
