@@ -12,13 +12,16 @@
 // factor row is kept both in LDS (the back substitution reads its columns)
 // and in registers, where the factorisation and the forward substitution
 // read it in unrolled loops.  Sums over components are butterfly
-// reductions inside the group (every lane ends with the same bits:
-// floating-point addition is commutative), vectors that every row needs are
+// reductions inside the group, vectors that every row needs are
 // broadcast through the LDS region, and the back substitution reads the
-// factor's columns there.  The
-// mixture's scalars (cubic root, trust radius, counters, decisions) are
-// computed identically in every lane of the group, so a group always takes
-// one path.  The arithmetic is that of the per-lane items in flash_stages.hpp
+// factor's columns there.  Every lane of the group computes the mixture's
+// scalars (cubic root, trust radius, objective), but not to the last bit: where
+// the summand is a product, the compiler fuses it into a reduction's first
+// addition, and each lane then holds its own summand unrounded and its
+// neighbour's rounded.  A group has to take one path all the same (its lanes
+// exchange values at every step, and the stage's loop counts on their ending
+// together), so every decision is the group's first lane's (Grp::uni).
+// The arithmetic is that of the per-lane items in flash_stages.hpp
 // (Appendix B.1 and B.2, readings as listed there); only the order of the
 // sums differs.
 #pragma once
@@ -107,6 +110,11 @@ struct Grp {
     // this lane's row of H = M + diag(dadd) without the addend (row NC
     // beyond the components)
     __device__ __forceinline__ double *hr() const { return sh + GroupLds<NC, G>::H + row * LD; }
+    // the first lane's decision, in every lane of the group
+    __device__ __forceinline__ bool uni(bool c) const
+    {
+        return ((__ballot(c) >> base) & 1ull) != 0ull;
+    }
 };
 
 // Row gi of the table kappa_ij = 1 - k_ij of the caller's mixture: for a
@@ -151,7 +159,7 @@ __device__ __forceinline__ void phase_eval_g(PhaseG &o, const Grp<NC, G> &g, dou
     const double A = gsum<G>(g.act ? t * psi : 0.0);
     const double B = gsum<G>(c * b);
     fl += Cost<NC>::mix;
-    cubic_root(A, B, o.Z, o.L, o.lzb, o.nroots, fl, zs);
+    cubic_root(A, B, o.Z, o.L, o.lzb, o.nroots, fl, zs, [&](bool v) { return g.uni(v); });
     o.A = A;
     o.B = B;
     const double ib = 1.0 / B;
@@ -219,7 +227,7 @@ __device__ __forceinline__ void phase_derivs_g(double &hdiag, const PhaseG &o,
 // lr (registers: the loops over it run unrolled, so that a lane's own
 // factor entries are register reads and each multiply-add reads one LDS
 // value, broadcast), 1/L_ii of this row in dinv.  Returns whether every
-// pivot was positive (the same in every lane).  As cholesky.
+// pivot was positive (the group's decision).  As cholesky.
 template <int NC, int G>
 __device__ __forceinline__ bool chol_g(double (&lr)[NC], double &dinv, double dadd,
                                        double shift, const Grp<NC, G> &g, uint32_t &fl)
@@ -246,7 +254,7 @@ __device__ __forceinline__ bool chol_g(double (&lr)[NC], double &dinv, double da
     }
     dinv = 1.0 / mine[g.act ? g.gi : 0];
     fl += Cost<NC>::chol;
-    return ok;
+    return g.uni(ok);
 }
 
 // y = L^-1 b (forward substitution; this lane's entries of b and y, its
@@ -325,8 +333,8 @@ __device__ __forceinline__ double trust_step_g(double &u, double &radius, bool &
         u = upper_solve_g<NC, G>(dinv, y, g);
         fl += Cost<NC>::trisolve;
         const double nu = sqrt(gsum<G>(u * u));
-        if (!(radius > 0.0)) radius = nu;
-        if (nu <= radius) {
+        if (g.uni(!(radius > 0.0))) radius = nu;
+        if (g.uni(nu <= radius)) {
             eta0 = true;
             have = true;
         } else {
@@ -335,7 +343,7 @@ __device__ __forceinline__ double trust_step_g(double &u, double &radius, bool &
             eta1 = (nu / nq) * (nu / nq) * (nu - radius) / radius;
             fl += NC * NC + 2 * NC + 6;
         }
-    } else if (!(radius > 0.0)) {
+    } else if (g.uni(!(radius > 0.0))) {
         radius = 1.0;
     }
     if (newton_only) return 0.0;
@@ -350,7 +358,7 @@ __device__ __forceinline__ double trust_step_g(double &u, double &radius, bool &
         double elo = fmax(0.0, -hmin);
         double ehi = sqrt(gsum<G>(gv * gv)) / radius + rowmax;
         double eta = elo > 0.0 ? elo : 1e-3 * ehi;
-        if (eta1 > 0.0 && eta1 < ehi) eta = eta1;
+        if (g.uni(eta1 > 0.0 && eta1 < ehi)) eta = eta1;
         for (int it = 0; it < 12; ++it) {
             if (!chol_g<NC, G>(lr, dinv, dadd, eta, g, fl)) {
                 elo = eta;
@@ -363,12 +371,12 @@ __device__ __forceinline__ double trust_step_g(double &u, double &radius, bool &
             const double nu = sqrt(gsum<G>(ut * ut));
             u = ut;
             have = true;
-            if (nu > 0.9 * radius && nu < 1.1 * radius) break;
-            if (nu > radius) elo = eta; else ehi = eta;
+            if (g.uni(nu > 0.9 * radius && nu < 1.1 * radius)) break;
+            if (g.uni(nu > radius)) elo = eta; else ehi = eta;
             const double q = lower_solve_g<NC, G>(lr, dinv, ut, g);
             const double nq = sqrt(gsum<G>(q * q));
             double en = eta + (nu / nq) * (nu / nq) * (nu - radius) / radius;
-            if (!(en > elo && en < ehi)) en = fmax(sqrt(elo * ehi), elo + 1e-3 * (ehi - elo));
+            if (g.uni(!(en > elo && en < ehi))) en = fmax(sqrt(elo * ehi), elo + 1e-3 * (ehi - elo));
             eta = en;
         }
         if (!have) {
@@ -376,7 +384,7 @@ __device__ __forceinline__ double trust_step_g(double &u, double &radius, bool &
             const double gg = gsum<G>(gv * gv);
             const double ghg = gsum<G>(gv * hg);
             const double tmax = radius / sqrt(gg);
-            const double t = (ghg > 0.0) ? fmin(gg / ghg, tmax) : tmax;
+            const double t = g.uni(ghg > 0.0) ? fmin(gg / ghg, tmax) : tmax;
             u = -t * gv;
             fl += 2 * NC * NC + 4 * NC;
         }
@@ -407,13 +415,13 @@ __device__ __forceinline__ auto kappa_of(const Ctx<NC> &c, int64_t m, const Grp<
 // ss_update): this lane's entries v, prev, s; returns ext.
 template <int NC, int G>
 __device__ __forceinline__ double ss_update_g(double &v, double &prev, double s, int u, int dem,
-                                              uint32_t &fl)
+                                              const Grp<NC, G> &g, uint32_t &fl)
 {
     double ext = 0.0;
     if (dem > 0 && u >= 2 && (u % dem) == 0) {
         const double num = gsum<G>(s * s), den = gsum<G>(prev * s);
         const double lam = num / den;
-        if (lam > 0.0 && lam < 1.0) ext = lam / (1.0 - lam);
+        if (g.uni(lam > 0.0 && lam < 1.0)) ext = lam / (1.0 - lam);
         fl += 4 * NC + 3;
     }
     v += s + ext * s;
@@ -430,10 +438,10 @@ __device__ __forceinline__ bool rr_solve_g(double z, double K, double &th, const
 {
     const double kmax = gmax<G>(g.act ? K : -INFINITY);
     const double kmin = gmin<G>(g.act ? K : INFINITY);
-    if (!(kmax > 1.0) || !(kmin < 1.0)) return false;
+    if (g.uni(!(kmax > 1.0) || !(kmin < 1.0))) return false;
     const double al = 1.0 / (1.0 - kmax), ar = 1.0 / (1.0 - kmin);
     double lo = al, hi = ar;
-    double t = (th > al && th < ar) ? th : 0.5;
+    double t = g.uni(th > al && th < ar) ? th : 0.5;
     const double c = K - 1.0;
     int it = 0;
     for (; it < 200; ++it) {
@@ -441,17 +449,17 @@ __device__ __forceinline__ bool rr_solve_g(double z, double K, double &th, const
         const double u = z * c * r;
         const double f = gsum<G>(u);
         const double fp = -gsum<G>(u * c * r);
-        if (f > 0.0) lo = t; else hi = t;
+        if (g.uni(f > 0.0)) lo = t; else hi = t;
         const double da = t - al, db = ar - t;
         const double h = da * db * f;
         const double hp = (db - da) * f + da * db * fp;
         const double tn = t - h / hp;
-        if (fabs(tn - t) < 1e-8) {
+        if (g.uni(fabs(tn - t) < 1e-8)) {
             t = fmin(fmax(tn, lo), hi);
             break;
         }
-        t = (tn > lo && tn < hi) ? tn : 0.5 * (lo + hi);
-        if (!(hi - lo > 0.0)) break;
+        t = g.uni(tn > lo && tn < hi) ? tn : 0.5 * (lo + hi);
+        if (g.uni(!(hi - lo > 0.0))) break;
     }
     fl += Cost<NC>::rr_iter * (uint32_t)(it + 1);
     th = t;
@@ -554,22 +562,22 @@ struct SaSsGroup {
         const double tm = 1.0 + gsum<G>(W * (grad - 1.0));
         const double gmx = gmax<G>(fabs(grad));
         fl += 6 * NC;
-        if (tm < -a.eps_tm || gmx < a.tol_sa_ss) {
+        if (g.uni(tm < -a.eps_tm || gmx < a.tol_sa_ss)) {
             done(c, tm, false, g);
             return true;
         }
         if (dem) {
             // an extrapolated point is kept only if it lowers tm
             dem = false;
-            if (!(tm < tmb)) {
+            if (g.uni(!(tm < tmb))) {
                 lw -= ext * prev;
                 if (++steps < kStepGuard) return false;
             }
         }
         if (ss < a.max_ss && ++steps < kStepGuard) {
-            ext = ss_update_g<NC, G>(lw, prev, -grad, ss + 1, a.dem_every, fl);
+            ext = ss_update_g<NC, G>(lw, prev, -grad, ss + 1, a.dem_every, g, fl);
             ++ss;
-            if (ext > 0.0) {
+            if (g.uni(ext > 0.0)) {
                 dem = true;
                 tmb = tm;
             }
@@ -692,7 +700,7 @@ struct SpSsGroup {
             // an extrapolated point is kept only if it is a physical split and
             // lowers G
             dem = false;
-            if (!(theta > 0.0 && theta < 1.0 && G_ < sgb)) {
+            if (g.uni(!(theta > 0.0 && theta < 1.0 && G_ < sgb))) {
                 lk -= sext * prev;
                 if (++steps < kStepGuard) return false;
             }
@@ -700,13 +708,14 @@ struct SpSsGroup {
         const double sv = g.act ? (r0 - o.lnphi) - lk : 0.0;
         const double dmax = gmax<G>(g.act ? fabs(exp(sv) - 1.0) : 0.0);
         fl += 4 * NC;
-        const bool conv = dmax < a.tol_split_ss;
+        const bool conv = g.uni(dmax < a.tol_split_ss);
         const bool more = !conv && ss + 1 < a.max_ss && steps + 1 < kStepGuard;
-        const double ext = ss_update_g<NC, G>(lk, prev, sv, ss + 1, more ? a.dem_every : 0, fl);
+        const double ext = ss_update_g<NC, G>(lk, prev, sv, ss + 1, more ? a.dem_every : 0, g,
+                                               fl);
         ++ss;
         if (more) {
             ++steps;
-            if (ext > 0.0) {
+            if (g.uni(ext > 0.0)) {
                 dem = true;
                 sgb = G_;
                 sext = ext;
@@ -719,7 +728,7 @@ struct SpSsGroup {
             restart_or_fail(c, true, conv ? 0u : kStSplitTr, g);
             return true;
         }
-        if (!(theta > 0.0 && theta < 1.0)) {
+        if (g.uni(!(theta > 0.0 && theta < 1.0))) {
             restart_or_fail(c, false, conv ? 0u : kStSplitTr, g);
             return true;
         }
@@ -805,11 +814,11 @@ struct SaTrGroup {
             pend = false;
             bool accept;
             double ratio = 1.0;
-            if (fabs(pred) < 1e-13) {
-                accept = gmx < gacc;
+            if (g.uni(fabs(pred) < 1e-13)) {
+                accept = g.uni(gmx < gacc);
             } else {
                 ratio = (tm - facc) / pred;
-                accept = (tm < facc) && ratio > 0.0;
+                accept = g.uni((tm < facc) && ratio > 0.0);
             }
             // a rejected or poor step halves the radius, from the length of
             // the step taken when the boundary cut made it shorter
@@ -821,10 +830,10 @@ struct SaTrGroup {
                 done(c, facc, g);
                 return true;
             }
-            if (ratio <= 0.25) rad = 0.5 * fmin(rad, slen);
-            else if (ratio >= 0.75) rad *= 2.0;
+            if (g.uni(ratio <= 0.25)) rad = 0.5 * fmin(rad, slen);
+            else if (g.uni(ratio >= 0.75)) rad *= 2.0;
         }
-        if (tm < -a.eps_tm || gmx < a.tol_sa_tr) {
+        if (g.uni(tm < -a.eps_tm || gmx < a.tol_sa_tr)) {
             done(c, tm, g);
             return true;
         }
@@ -844,7 +853,7 @@ struct SaTrGroup {
         double pr = trust_step_g<NC, G>(u, rad, eta0, dinv, hdiag, dadd, gv, g, fl);
         const double amax = gmin<G>((g.act && u < 0.0) ? cut_step(1.0, 2.0 * sqrt(W), -u) : 1.0);
         slen = amax * sqrt(gsum<G>(g.act ? u * u : 0.0));
-        if (amax < 1.0) {
+        if (g.uni(amax < 1.0)) {
             const double gu = gsum<G>(gv * u);
             pr = amax * gu + amax * amax * (pr - gu);
         }
@@ -990,10 +999,12 @@ struct SpNtGroup {
         double x, y, bv;
         xy_from_nv(x, y, bv);
         const double lk = gmax<G>(g.act ? fabs(log(y / x)) : 0.0);
-        const bool degenerate = !(bv > kMinPhase && bv < 1.0 - kMinPhase);
-        const bool stalled = (status & kStSplitUnconv) && fmin(bv, 1.0 - bv) < kStalledPhase;
-        if ((degenerate || lk < 1e-6 || stalled) && !restarted && r.wsel >= 0) {
-            if (stalled && !degenerate && !(lk < 1e-6)) {
+        const bool degenerate = g.uni(!(bv > kMinPhase && bv < 1.0 - kMinPhase));
+        const bool trivial = g.uni(lk < 1e-6);
+        const bool stalled =
+            (status & kStSplitUnconv) && g.uni(fmin(bv, 1.0 - bv) < kStalledPhase);
+        if ((degenerate || trivial || stalled) && !restarted && r.wsel >= 0) {
+            if (stalled && !degenerate && !trivial) {
                 if (g.act) r.lk[g.gi] = v0;
                 back = true;
             }
@@ -1001,7 +1012,7 @@ struct SpNtGroup {
             status = (status & ~(kStSplitUnconv | kStStepCap)) | kStSplitTr | kStSplitRestart;
             return false;
         }
-        if ((degenerate || lk < 1e-6) && back) {
+        if ((degenerate || trivial) && back) {
             // the restarted descent failed: the stalled split is the result
             back_to_stalled(c, g);
             return false;
@@ -1010,11 +1021,11 @@ struct SpNtGroup {
             write_single(c, g, status | kStSplitFailed, it);
             return true;
         }
-        if (lk < 1e-6) {
+        if (trivial) {
             write_single(c, g, status | kStSplitTrivial, it);
             return true;
         }
-        const bool swap = zx_ > zy_;
+        const bool swap = g.uni(zx_ > zy_);
         if (swap) status |= kStSwapped;
         if (g.act) {
             a.x[m * NC + g.gi] = swap ? y : x;
@@ -1074,7 +1085,7 @@ struct SpNtGroup {
         if (start) {
             // restart: the first point whose G is below the feed's starts the
             // trust region; otherwise halve the vapour amount
-            if (G_ < gf - 1e-12 * (1.0 + fabs(gf))) {
+            if (g.uni(G_ < gf - 1e-12 * (1.0 + fabs(gf)))) {
                 start = false;
             } else {
                 if (++nhalf > 30 || ++steps >= kStepGuard) {
@@ -1118,11 +1129,11 @@ struct SpNtGroup {
                 spend = false;
                 bool accept;
                 double ratio = 1.0;
-                if (fabs(spred) < 1e-13) {
-                    accept = gmx < sgacc;
+                if (g.uni(fabs(spred) < 1e-13)) {
+                    accept = g.uni(gmx < sgacc);
                 } else {
                     ratio = (G_ - sfacc) / spred;
-                    accept = (G_ < sfacc) && ratio > 0.0;
+                    accept = g.uni((G_ < sfacc) && ratio > 0.0);
                 }
                 // a rejected or poor step halves the radius, from the length of
                 // the step taken when the boundary cut made it shorter
@@ -1134,10 +1145,10 @@ struct SpNtGroup {
                     fin = 1;
                     break;
                 }
-                if (ratio <= 0.25) srad = 0.5 * fmin(srad, slen);
-                else if (ratio >= 0.75) srad *= 2.0;
+                if (g.uni(ratio <= 0.25)) srad = 0.5 * fmin(srad, slen);
+                else if (g.uni(ratio >= 0.75)) srad *= 2.0;
             }
-            if (!spol && !tronly && gmx < a.tol_split_tr) {
+            if (!spol && !tronly && g.uni(gmx < a.tol_split_tr)) {
                 spol = true;   // the paper's criterion holds: refine
                 sdprev = 1e300;
             }
@@ -1178,9 +1189,10 @@ struct SpNtGroup {
                 const double amax = gmin<G>(lim);
                 v0 += amax * u;
                 fl += 6 * NC;
-                const bool conv = dmax < a.tol_polish || (dmax < 1e-10 && dmax >= 0.5 * sdprev);
+                const bool conv =
+                    g.uni(dmax < a.tol_polish || (dmax < 1e-10 && dmax >= 0.5 * sdprev));
                 if (conv || pol >= a.max_polish || ++steps >= kStepGuard) {
-                    if (!conv && !(dmax < 1e-10)) status |= kStSplitUnconv;
+                    if (!conv && g.uni(!(dmax < 1e-10))) status |= kStSplitUnconv;
                     fin = 2;
                     break;
                 }
@@ -1194,7 +1206,7 @@ struct SpNtGroup {
             // inactive lanes hold u = 0
             const double lim = cut_step(1.0, u < 0.0 ? v0 : z - v0, fabs(u));
             const double amax = gmin<G>(lim);
-            if (amax < 1.0) {
+            if (g.uni(amax < 1.0)) {
                 const double gu = gsum<G>(gt * u);
                 pr = amax * gu + amax * amax * (pr - gu);
             }

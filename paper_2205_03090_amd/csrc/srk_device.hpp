@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace ptf {
 
 // SRK constants as printed with the combining rules (Appendix A, eqs. a_i, b_i)
@@ -99,6 +101,12 @@ __device__ __forceinline__ int gibbs_order(double A, double B, double zl, double
     return 0;
 }
 
+// Who decides where lanes work on one mixture together: by default each lane for
+// itself (flash_group.hpp: the group's first lane for all).
+struct OwnChoice {
+    __device__ __forceinline__ bool operator()(bool c) const { return c; }
+};
+
 // Minimum-Gibbs root of Z^3 - Z^2 + (A - B - B^2) Z - AB = 0 (eq. cubic_Z).
 // Halley's iteration (eq. halley) from the liquid-like start Z = B (or from
 // zs, the root chosen at the previous iterate of the same phase, when it lies
@@ -112,10 +120,12 @@ __device__ __forceinline__ int gibbs_order(double A, double B, double zl, double
 // correction on the full cubic; between the smallest (liquid) and largest
 // (vapour) root the one with the lower reduced residual Gibbs energy
 // g = Z - 1 - ln(Z - B) - (A/B) ln(1 + B/Z) is kept (ties go to the liquid).
-template <bool EACH = false>
+// uni makes the choice of the root common to lanes that hold the same cubic up to
+// rounding.
+template <bool EACH = false, class U = OwnChoice>
 __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, double &Lout,
                                            double &lzbout, int &nroots, uint32_t &fl,
-                                           double zs = -1.0)
+                                           double zs = -1.0, U uni = {})
 {
     const double r1 = A - B * (1.0 + B);
     const double r0 = A * B;
@@ -199,9 +209,13 @@ __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, dou
     // which single precision decides in all but 1e-5 of the evaluations; only
     // there are the candidates' energies formed in FP64.  10^6 mixtures at
     // nc 8: 3.80 -> 3.67 ms.
+    const bool several = uni(nroots > 1);
+    if constexpr (!std::is_same_v<U, OwnChoice>) {
+        if (!several) zl = Z;
+    }
     zl = pol(zl);
     bool vapour = false;
-    if (nroots > 1) {
+    if (several) {
         zv = pol(zv);
         fl += 2 * Cost<1>::polish + 2 * Cost<1>::gibbs;
         int sg = gibbs_order(A, B, zl, zv);
@@ -211,7 +225,7 @@ __device__ __forceinline__ void cubic_root(double A, double B, double &Zout, dou
             const double gv = zv - 1.0 - log(zv - B) - ab * log1p(B / zv);
             sg = gv < gl ? -1 : 1;
         }
-        vapour = sg < 0;
+        vapour = uni(sg < 0);
     } else {
         fl += Cost<1>::polish + 4;
     }
