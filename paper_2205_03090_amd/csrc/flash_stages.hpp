@@ -1554,11 +1554,11 @@ struct SpNtItem {
             }
             // dn = v o u, kept inside 0 < n^V < z
             // norm2 with its rounding fixed as in scale_sum (the order of two
-            // squares is the one this stage has always had)
+            // squares is the one that the compiler chose while it was left to it)
             double nu = 0.0;
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
-                const int i = (NC == 2 && PM) ? NC - 1 - k : k;
+                const int i = NC == 2 ? NC - 1 - k : k;
                 nu = fma(u[i], u[i], nu);
             }
             nu = sqrt(nu);
