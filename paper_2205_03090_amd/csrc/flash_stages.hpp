@@ -1423,7 +1423,7 @@ struct SpNtItem {
             const double fx = l0[i] + r0[i];
             const double fy = l1[i] + r1[i];
             gt[i] = fy - fx;
-            G += (z[i] - v0[i]) * fx + v0[i] * fy;
+            G = G + fma(z[i] - v0[i], fx, v0[i] * fy);   // rounding fixed as in scale_sum
             gmax = fmax(gmax, fabs(gt[i]));
             gs[i] = vs[i] * gt[i];
         }
