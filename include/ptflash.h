@@ -85,11 +85,15 @@ extern "C" {
                                      lanes.  With grid, block and the lanes
                                      options all 0, a batch of n mixtures runs
                                      as FUSED when n <= 300000 (nc <= 4),
-                                     150000 (nc <= 8), 120000 (nc <= 10),
-                                     70000 (nc <= 12) or n * nc <= 400000
-                                     (above), the smallest of these with a
-                                     team of lanes per mixture (n <= 20000 at
-                                     nc <= 4, n <= 10000 up to nc = 12)   */
+                                     150000 (nc <= 8), 120000 (nc = 9),
+                                     100000 (nc = 10), 70000 (nc <= 12) or
+                                     n * nc <= 400000 (above), the smallest
+                                     of these with a team of lanes per
+                                     mixture (n <= 20000 at nc <= 4, n <=
+                                     10000 up to nc = 12); the stability
+                                     analysis alone up to 90000 at nc = 9
+                                     and 10, and with teams for n <= 8192
+                                     (nc <= 4) and 4096 (nc <= 12)        */
 #define PTFLASH_FORM_PLAIN 1      /* one launch per stage iteration + compaction */
 #define PTFLASH_FORM_FUSED 2      /* one launch; a lane pair carries one mixture
                                      through every stage, its two stability

@@ -81,6 +81,21 @@ def current_table():
     return table("kTunedLanesSa"), table("kTunedLanesSp"), ss, table("kTunedBlock")
 
 
+def form_limits():
+    """The tables of csrc/form_limits.hpp: (team, fused), each
+    [0: flash, 1: stability analysis alone][nc]."""
+    import re
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "form_limits.hpp")
+    with open(path) as f:
+        text = f.read()
+
+    def table(name):
+        body = re.search(name + r"\[2\]\[21\] = \{(.*?)\};", text, re.S).group(1)
+        return [[int(v) for v in r.split(",")] for r in re.findall(r"\{([^{}]*)\}", body + "}")]
+
+    return table("kTeamMaxN"), table("kFusedMaxN")
+
+
 def header(lanes_sa, lanes_sp, lanes_ss, blocks) -> str:
     """lanes_sa etc.: [layout][nc], layout 0 = shared set, 1 = one per mixture."""
     def row(v):

@@ -25,6 +25,7 @@
 #include "flash_stages.hpp"
 #include "flash_group.hpp"
 #include "flash_team.hpp"
+#include "form_limits.hpp"
 #include "adjoint_device.hpp"
 #include "tuned_gfx950.hpp"
 
@@ -1141,20 +1142,8 @@ int launch_fused(const FlashArgs &a, const ptflash_problem *p, const ptflash_opt
     return hipGetLastError() == hipSuccess ? PTFLASH_OK : PTFLASH_EHIP;
 }
 
-// Batches up to this many mixtures run the fused form with a team of lanes per
-// mixture (0: never).  A team takes 8 or 16 lanes where the lane pair takes two
-// and needs about half the instructions per step, so it wins while the device has
-// lanes to spare.  Measured (MI355X, us per call, team against lane pairs): nc 3
-// 168 / 247 at 2000 mixtures, 248 / 314 at 16,000, 305 / 272 at 24,000; nc 4 352 / 351 at
-// 20,000; nc 5 254 / 383 at 4000, 378 / 393 at 8000, 473 / 433 at 12,000; nc 8 269 / 463 at
-// 1000, 481 / 557 at 10,000, 620 / 629 at 12,000; nc 10 607 / 650 at 10,000; nc 12 (own sets)
-// 893 / 1186 at 4000, 1247 / 1452 at 10,000, 1510 / 1203 at 12,000.
-template <int NC>
-constexpr int64_t team_max_n()
-{
-    return NC <= 4 ? 20000 : NC <= kTeamMaxNc ? 10000 : 0;
-}
-
+// The fused form with teams, for the smallest batches (form_limits.hpp).  A step
+// of a team issues about half the instructions of a lane's.
 template <int NC, bool PM>
 int launch_team(const FlashArgs &a, const ptflash_problem *p, void *ws, hipStream_t s)
 {
@@ -1212,35 +1201,17 @@ size_t nc_workspace_bytes(int64_t n, int form)
     return workspace_bytes<NC>(n, form);
 }
 
-// Batches up to this many mixtures run the persistent form as one fused
-// launch unless the caller sets its launch shape (grid, block or lanes per
-// mixture): below it the staged form's time is the sum of its stages'
-// slowest items, which the fused form's slowest whole path undercuts.  The
-// fused form keeps a whole mixture on one lane pair, so above nc 12, where
-// the staged form moves the trust-region work onto lane groups and the fused
-// form's tail has no teams, it pays off only for smaller batches.  Measured
-// (MI355X, us, staged / fused): nc 2 1223 / 1073 at 300,000, 1324 / 1403 at 400,000; nc 4
-// 1200 / 991 at 200,000, 1350 / 1372 at 300,000 (own sets 1671 / 1347); nc 5 1418 / 1312 at
-// 150,000, 1518 / 1709 at 200,000; nc 8 1448 / 1034 at 80,000, 1917 / 1596 at 150,000,
-// 1703 / 2056 at 200,000; nc 9 1644 / 1487 at 100,000, 1746 / 1775 at 130,000; nc 12 2682 / 2398
-// at 60,000, 2695 / 2676 at 80,000 (own sets 2893 / 3105).
-template <int NC>
-constexpr int64_t fused_max_n()
-{
-    return NC <= 4 ? 300000 : NC <= 8 ? 150000 : NC <= 10 ? 120000 : NC <= 12 ? 70000
-                                                                           : 400000 / NC;
-}
-
 template <int NC, bool PM>
 int nc_flash_pm(const FlashArgs &a, const ptflash_problem *p, const ptflash_options *o, void *ws,
                 hipStream_t s)
 {
     if (o->form == PTFLASH_FORM_PLAIN) return launch_plain<NC, PM>(a, p, ws, s);
     if (o->form == PTFLASH_FORM_FUSED) return launch_fused<NC, PM>(a, p, o, ws, s);
+    const int what = a.stability_only ? 1 : 0;
     if (o->grid <= 0 && o->block <= 0 && o->lanes_per_mixture <= 0 && o->lanes_split <= 0 &&
-        o->lanes_ss <= 0 && p->n <= fused_max_n<NC>()) {
-        if constexpr (team_max_n<NC>() > 0) {
-            if (p->n <= team_max_n<NC>()) return launch_team<NC, PM>(a, p, ws, s);
+        o->lanes_ss <= 0 && p->n <= kFusedMaxN[what][NC]) {
+        if constexpr (NC <= kTeamMaxNc) {
+            if (p->n <= kTeamMaxN[what][NC]) return launch_team<NC, PM>(a, p, ws, s);
         }
         ptflash_options f = *o;
         f.block = 64;
