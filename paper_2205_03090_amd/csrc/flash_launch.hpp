@@ -518,6 +518,18 @@ constexpr bool fused_tail_ok()
     return NC <= kTeamMaxNc;
 }
 
+// Component counts whose fused form runs the stability trials without the shortcuts
+// that keep more values live (SoloStraight): those whose kernel spills a lane's
+// matrices to scratch.  Stability analyses, us, with / without the shortcuts: nc 16
+// 1251 / 1110 at 10,000 mixtures, nc 17 1268 / 1223 (own sets at 4000 1292 / 1224), nc 20 (own
+// sets) 2325 / 2206 at 10,000; nc 13 the same; flashes the same or 1 % less.  (The staged
+// form's trials are kernels of their own: nc 17 at 70,000 2824 / 2933.)
+template <int NC>
+constexpr bool fused_straight()
+{
+    return NC > kTeamMaxNc;
+}
+
 // Wavefronts per SIMD that the fused form's registers are to allow: up to nc 4 it
 // reached two by itself, but does not around a call.
 template <int NC>
@@ -574,9 +586,10 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     if (route == L_SA) {
         // trial t in lane t, then the decision (list L_SAFIN) in the first lane
+        using S = std::conditional_t<fused_straight<NC>(), SoloStraight, Solo>;
         Outbox q;
-        fused_item<SaSsItem<NC, PM>, NC>(c, 2 * id + t, q);
-        if (q.l0 == L_SATR) fused_item<SaTrItem<NC, PM>, NC>(c, 2 * id + t, q);
+        fused_item<SaSsItem<NC, PM, S>, NC>(c, 2 * id + t, q);
+        if (q.l0 == L_SATR) fused_item<SaTrItem<NC, PM, S>, NC>(c, 2 * id + t, q);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         if (t == 0) fused_item<SaFinItem<NC, PM>, NC>(c, id, o);
     }

@@ -188,12 +188,22 @@ struct Outbox {
 // relatives apply a function to every element of a per-component array.
 struct Solo {
     static constexpr bool kTeam = false;
+    // One end of the cubic for all its cases, and quotients only where they
+    // matter: shorter, but more values stay live across them.
+    static constexpr bool kBranchy = true;
     template <int NC, class F>
     static __device__ __forceinline__ void map(double (&v)[NC], F f)
     {
 #pragma unroll
         for (int i = 0; i < NC; ++i) v[i] = f(v[i]);
     }
+};
+
+// One lane's work, for the stability trials of kernels that spill anyway: each case
+// of the cubic forms its own logarithms, and every quotient is formed.
+struct SoloStraight {
+    static constexpr bool kTeam = false;
+    static constexpr bool kBranchy = false;
 };
 
 // ---------------------------------------------------------------------------
@@ -733,7 +743,7 @@ struct SaSsItem {
         for (int i = 0; i < NC; ++i) W[i] = exp(lw[i]);
         fl += NC;
         Phase<NC> o;
-        phase_eval<NC>(o, e, pp.K, W, fl, zw);
+        phase_eval<NC, !X::kBranchy>(o, e, pp.K, W, fl, zw);
         zw = o.Z;
         double grad[NC], tm = 1.0, gmax = 0.0;
 #pragma unroll
@@ -845,7 +855,7 @@ struct SaTrItem {
         for (int i = 0; i < NC; ++i) W[i] = exp(lw[i]);
         fl += NC;
         Phase<NC> o;
-        phase_eval<NC>(o, e, pp.K, W, fl, zw);
+        phase_eval<NC, !X::kBranchy>(o, e, pp.K, W, fl, zw);
         zw = o.Z;
         double F[NP], Hs[NP], dinv[NC];
         phase_derivs<NC>(F, o, e, pp.K, fl);
@@ -909,7 +919,12 @@ struct SaTrItem {
         double amax = 1.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            if (u[i] < 0.0) amax = cut_step(amax, 2.0 * sqrt(W[i]), -u[i]);
+            if constexpr (X::kBranchy) {
+                if (u[i] < 0.0) amax = cut_step(amax, 2.0 * sqrt(W[i]), -u[i]);
+            } else {
+                const double bi = 2.0 * sqrt(W[i]);
+                if (u[i] < 0.0) amax = fmin(amax, 0.99 * bi / -u[i]);
+            }
         }
         slen = amax * norm2<NC>(u);
         if (amax < 1.0) {
