@@ -518,12 +518,13 @@ constexpr bool fused_tail_ok()
     return NC <= kTeamMaxNc;
 }
 
-// Component counts whose fused form runs the stability trials without the shortcuts
-// that keep more values live (SoloStraight): those whose kernel spills a lane's
-// matrices to scratch.  Stability analyses, us, with / without the shortcuts: nc 16
-// 1251 / 1110 at 10,000 mixtures, nc 17 1268 / 1223 (own sets at 4000 1292 / 1224), nc 20 (own
-// sets) 2325 / 2206 at 10,000; nc 13 the same; flashes the same or 1 % less.  (The staged
-// form's trials are kernels of their own: nc 17 at 70,000 2824 / 2933.)
+// Component counts whose fused form does without the shortcuts that keep more values
+// live (SoloStraight): those whose kernel spills a lane's matrices to scratch.  us, with
+// / without the shortcuts: stability analyses nc 16 1251 / 1110 at 10,000 mixtures,
+// nc 17 1268 / 1223 (own sets at 4000 1292 / 1224), nc 20 (own sets) 2325 / 2206 at 10,000,
+// nc 13 the same; warm starts (own sets) nc 17 8332 / 8222 at 3000, nc 20 15,340 / 15,034 at
+// 19,000; flashes 0 to 2 % less.  (The staged form's trials are kernels of their own:
+// nc 17 at 70,000 2824 / 2933.)
 template <int NC>
 constexpr bool fused_straight()
 {
@@ -575,6 +576,7 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     const bool in = m < c.a.n;   // both lanes of the pair
     if (!TAIL && !in) return;
     const uint32_t id = (uint32_t)m;
+    using S = std::conditional_t<fused_straight<NC>(), SoloStraight, Solo>;
     Outbox o;
     o.clear();
     if (in && t == 0) {
@@ -586,7 +588,6 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     if (route == L_SA) {
         // trial t in lane t, then the decision (list L_SAFIN) in the first lane
-        using S = std::conditional_t<fused_straight<NC>(), SoloStraight, Solo>;
         Outbox q;
         fused_item<SaSsItem<NC, PM, S>, NC>(c, 2 * id + t, q);
         if (q.l0 == L_SATR) fused_item<SaTrItem<NC, PM, S>, NC>(c, 2 * id + t, q);
@@ -604,7 +605,7 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     } else {
         if (t != 0 || o.l0 != L_SPLIT) return;
         fused_item<SpSsItem<NC, PM>, NC>(c, id, o);
-        if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM>, NC>(c, id, o);
+        if (o.l0 == L_NT || o.l0 == L_NTP) fused_item<SpNtItem<NC, PM, S>, NC>(c, id, o);
     }
 }
 

@@ -199,8 +199,9 @@ struct Solo {
     }
 };
 
-// One lane's work, for the stability trials of kernels that spill anyway: each case
-// of the cubic forms its own logarithms, and every quotient is formed.
+// One lane's work, for kernels that spill anyway: in a stability trial each case of
+// the cubic forms its own logarithms and every quotient is formed, and the end of a
+// split forms the logarithms that tell a trivial one.
 struct SoloStraight {
     static constexpr bool kTeam = false;
     static constexpr bool kBranchy = false;
@@ -359,16 +360,18 @@ __device__ __forceinline__ double ss_far(double tol)
 
 // Whether two compositions agree to max_i |ln(y_i/x_i)| < 1e-6 (a trivial
 // split).  A component that is clearly further apart settles the answer
-// without a logarithm; only where none is are the logarithms formed.
-template <int NC>
+// without a logarithm; only where none is are the logarithms formed (SHORT).
+template <int NC, bool SHORT = true>
 __device__ __forceinline__ bool trivial_split(const double (&x)[NC], const double (&y)[NC])
 {
-    bool far = false;
+    if constexpr (SHORT) {
+        bool far = false;
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-        far = far || (x[i] > 0.0 && (y[i] > x[i] * (1.0 + 4e-6) ||
-                                     (y[i] >= 0.0 && y[i] < x[i] * (1.0 - 4e-6))));
-    if (far) return false;
+        for (int i = 0; i < NC; ++i)
+            far = far || (x[i] > 0.0 && (y[i] > x[i] * (1.0 + 4e-6) ||
+                                         (y[i] >= 0.0 && y[i] < x[i] * (1.0 - 4e-6))));
+        if (far) return false;
+    }
     double lk = 0.0;
 #pragma unroll
     for (int i = 0; i < NC; ++i) lk = fmax(lk, fabs(log(y[i] / x[i])));
@@ -1314,7 +1317,7 @@ struct SpNtItem {
         it[7] = (int16_t)pol;
         double x[NC], y[NC], bv;
         xy_from_nv(x, y, bv);
-        const bool trivial = trivial_split<NC>(x, y);
+        const bool trivial = trivial_split<NC, X::kBranchy>(x, y);
         const bool degenerate = !(bv > kMinPhase && bv < 1.0 - kMinPhase);
         const bool stalled = (status & kStSplitUnconv) && fmin(bv, 1.0 - bv) < kStalledPhase;
         if ((degenerate || trivial || stalled) && !restarted && r.wsel >= 0) {
