@@ -518,18 +518,20 @@ constexpr bool fused_tail_ok()
     return NC <= kTeamMaxNc;
 }
 
-// Component counts whose fused form does without the shortcuts that keep more values
-// live (SoloStraight): those whose kernel spills a lane's matrices to scratch.  us, with
-// / without the shortcuts: stability analyses nc 16 1251 / 1110 at 10,000 mixtures,
-// nc 17 1268 / 1223 (own sets at 4000 1292 / 1224), nc 20 (own sets) 2325 / 2206 at 10,000,
-// nc 13 the same; warm starts (own sets) nc 17 8332 / 8222 at 3000, nc 20 15,340 / 15,034 at
-// 19,000; flashes 0 to 2 % less.  (The staged form's trials are kernels of their own:
-// nc 17 at 70,000 2824 / 2933.)
+// The items of the fused form's lane pairs: without the shortcuts that keep more values
+// live (SoloAs) where the kernel spills a lane's matrices to scratch and is slower with
+// them.  us, with all shortcuts / without those named:
+//   a trial's quotients on need, nc > 12: stability analyses nc 14 433 / 404 at 300
+//   mixtures, own sets 735 / 713 at 3000;
+//   the cubic's one end too, nc > 15: stability analyses nc 16 1251 / 1110 at 10,000, nc 17
+//   (own sets) 1292 / 1224 at 4000, nc 20 (own sets) 2325 / 2206 at 10,000 (but nc 14 404 / 433
+//   at 300);
+//   the split's end too, nc > 16: warm starts (own sets) nc 17 8332 / 8222 at 3000, nc 20
+//   15,340 / 15,034 at 19,000 (but nc 16 5421 / 5529 at 9800).
+// (The staged form's trials are kernels of their own: nc 17 at 70,000 2824 with, 2933
+// without.)
 template <int NC>
-constexpr bool fused_straight()
-{
-    return NC > kTeamMaxNc;
-}
+using PairItems = SoloAs<(NC <= 15), (NC <= kTeamMaxNc), (NC <= 16)>;
 
 // Wavefronts per SIMD that the fused form's registers are to allow: up to nc 4 it
 // reached two by itself, but does not around a call.
@@ -576,7 +578,7 @@ stage_fused(Ctx<NC> c, const double *__restrict__ Tc, const double *__restrict__
     const bool in = m < c.a.n;   // both lanes of the pair
     if (!TAIL && !in) return;
     const uint32_t id = (uint32_t)m;
-    using S = std::conditional_t<fused_straight<NC>(), SoloStraight, Solo>;
+    using S = PairItems<NC>;
     Outbox o;
     o.clear();
     if (in && t == 0) {

@@ -186,11 +186,15 @@ struct Outbox {
 // How the items below use the lanes of a wavefront.  Solo: an item is one
 // lane's work.  (A team of lanes per item: flash_team.hpp.)  map and its
 // relatives apply a function to every element of a per-component array.
-struct Solo {
+template <bool SHORT_CUBIC, bool SHORT_CUT, bool SHORT_END>
+struct SoloAs {
     static constexpr bool kTeam = false;
-    // One end of the cubic for all its cases, and quotients only where they
-    // matter: shorter, but more values stay live across them.
-    static constexpr bool kBranchy = true;
+    // Shorter, but more values stay live across them (where they pay:
+    // flash_launch.hpp): in a stability trial, one end of the cubic for all its cases
+    // and quotients of a step only where they matter; at the end of a split, no
+    // logarithms to tell a trivial one.
+    static constexpr bool kShortCubic = SHORT_CUBIC, kShortCut = SHORT_CUT,
+                          kShortEnd = SHORT_END;
     template <int NC, class F>
     static __device__ __forceinline__ void map(double (&v)[NC], F f)
     {
@@ -198,14 +202,7 @@ struct Solo {
         for (int i = 0; i < NC; ++i) v[i] = f(v[i]);
     }
 };
-
-// One lane's work, for kernels that spill anyway: in a stability trial each case of
-// the cubic forms its own logarithms and every quotient is formed, and the end of a
-// split forms the logarithms that tell a trivial one.
-struct SoloStraight {
-    static constexpr bool kTeam = false;
-    static constexpr bool kBranchy = false;
-};
+using Solo = SoloAs<true, true, true>;
 
 // ---------------------------------------------------------------------------
 // Shared helpers
@@ -746,7 +743,7 @@ struct SaSsItem {
         for (int i = 0; i < NC; ++i) W[i] = exp(lw[i]);
         fl += NC;
         Phase<NC> o;
-        phase_eval<NC, !X::kBranchy>(o, e, pp.K, W, fl, zw);
+        phase_eval<NC, !X::kShortCubic>(o, e, pp.K, W, fl, zw);
         zw = o.Z;
         double grad[NC], tm = 1.0, gmax = 0.0;
 #pragma unroll
@@ -858,7 +855,7 @@ struct SaTrItem {
         for (int i = 0; i < NC; ++i) W[i] = exp(lw[i]);
         fl += NC;
         Phase<NC> o;
-        phase_eval<NC, !X::kBranchy>(o, e, pp.K, W, fl, zw);
+        phase_eval<NC, !X::kShortCubic>(o, e, pp.K, W, fl, zw);
         zw = o.Z;
         double F[NP], Hs[NP], dinv[NC];
         phase_derivs<NC>(F, o, e, pp.K, fl);
@@ -922,7 +919,7 @@ struct SaTrItem {
         double amax = 1.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            if constexpr (X::kBranchy) {
+            if constexpr (X::kShortCut) {
                 if (u[i] < 0.0) amax = cut_step(amax, 2.0 * sqrt(W[i]), -u[i]);
             } else {
                 const double bi = 2.0 * sqrt(W[i]);
@@ -1317,7 +1314,7 @@ struct SpNtItem {
         it[7] = (int16_t)pol;
         double x[NC], y[NC], bv;
         xy_from_nv(x, y, bv);
-        const bool trivial = trivial_split<NC, X::kBranchy>(x, y);
+        const bool trivial = trivial_split<NC, X::kShortEnd>(x, y);
         const bool degenerate = !(bv > kMinPhase && bv < 1.0 - kMinPhase);
         const bool stalled = (status & kStSplitUnconv) && fmin(bv, 1.0 - bv) < kStalledPhase;
         if ((degenerate || trivial || stalled) && !restarted && r.wsel >= 0) {

@@ -26,7 +26,7 @@ namespace ptf {
 template <int D, int WAVES = 1>
 struct Team {
     static constexpr bool kTeam = true;
-    static constexpr bool kBranchy = true;
+    static constexpr bool kShortCubic = true, kShortCut = true, kShortEnd = true;
     static constexpr int kLanes = 2 * D;
     static constexpr int kPerWave = 64 / kLanes;
 
