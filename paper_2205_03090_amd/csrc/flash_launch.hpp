@@ -1131,7 +1131,8 @@ int run_plain_stage(const Ctx<NC> &c, const ptflash_problem *p, char *tail, hipS
                        p->Pc, p->omega, p->kij, states, la, na);
     int64_t nact = 0;
     if ((rc = read_count(na, nact, s))) return rc;
-    for (int guard = 0; nact > 0 && guard <= kStepGuard + 1; ++guard) {
+    // kStepGuard steps end an item, or start it once more (the restart of a split)
+    for (int guard = 0; nact > 0 && guard <= 2 * kStepGuard + 8; ++guard) {
         hipLaunchKernelGGL(reset_counters, dim3(1), dim3(64), 0, s, nb, 1);
         hipLaunchKernelGGL((stage_plain_step<Item, NC>), grid(nact), dim3(kBlock), 0, s, c, p->Tc,
                            p->Pc, p->omega, p->kij, states, la, nact, lb, nb);
