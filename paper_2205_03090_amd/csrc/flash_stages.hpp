@@ -1276,8 +1276,10 @@ struct SpNtItem {
         tr0 = tr - c.a.max_tr_split;
     }
 
-    // x, y from v0 = n^V: y = n^V/sum n^V, x = (z - n^V)/sum(z - n^V)
-    __device__ __forceinline__ void xy_from_nv(double (&x)[NC], double (&y)[NC], double &bv)
+    // x, y from v0 = n^V: y = n^V/sum n^V, x = (z - n^V)/sum(z - n^V); sx, sy:
+    // the sums of the two, for the phase evaluations
+    __device__ __forceinline__ void xy_from_nv(double (&x)[NC], double (&y)[NC], double &bv,
+                                               double &sx, double &sy)
     {
         double sv = 0.0, sl = 0.0;
 #pragma unroll
@@ -1287,9 +1289,8 @@ struct SpNtItem {
             sv += y[i];
             sl += x[i];
         }
-        const double iv = 1.0 / sv, il = 1.0 / sl;
-#pragma unroll
-        for (int i = 0; i < NC; ++i) { x[i] *= il; y[i] *= iv; }
+        sx = scale_sum<NC, true>(x, 1.0 / sl);
+        sy = scale_sum<NC, true>(y, 1.0 / sv);
         bv = sv;
         fl += 5 * NC + 2;
     }
@@ -1312,8 +1313,8 @@ struct SpNtItem {
         load_it<NC>(it, r);
         it[6] = (int16_t)tr;
         it[7] = (int16_t)pol;
-        double x[NC], y[NC], bv;
-        xy_from_nv(x, y, bv);
+        double x[NC], y[NC], bv, sx, sy;
+        xy_from_nv(x, y, bv, sx, sy);
         const bool trivial = trivial_split<NC, X::kShortEnd>(x, y);
         const bool degenerate = !(bv > kMinPhase && bv < 1.0 - kMinPhase);
         const bool stalled = (status & kStSplitUnconv) && fmin(bv, 1.0 - bv) < kStalledPhase;
@@ -1370,8 +1371,8 @@ struct SpNtItem {
     {
         const Props pp = mix_props<NC, PM>(c.pr, m);
         const FlashArgs &a = c.a;
-        double w0[NC], w1[NC], bvap;
-        xy_from_nv(w0, w1, bvap);
+        double w0[NC], w1[NC], bvap, s0, s1;
+        xy_from_nv(w0, w1, bvap, s0, s1);
         // scaled Hessian H' = (I - v v' + V((1-th) Phi^V + th Phi^L)V)/(th(1-th)),
         // v_i = sqrt(x_i y_i / z_i), accumulated over the two evaluations
         double vs[NC];
@@ -1390,16 +1391,6 @@ struct SpNtItem {
         Phase<NC> o;
         if constexpr (X::kTeam) {
             // the two phases side by side; then both lanes hold both results
-            double x[NC], y[NC], sv = 0.0, sl = 0.0;
-#pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                x[i] = z[i] - v0[i];
-                y[i] = v0[i];
-                sv += y[i];
-                sl += x[i];
-            }
-            const double s0 = scale_sum<NC, true>(x, 1.0 / sl);
-            const double s1 = scale_sum<NC, true>(y, 1.0 / sv);
             X::template log_pair<NC>(l0, l1, w0, w1);
             X::template eval_pair<NC>(o, e, pp.K, w0, w1, s0, s1, zx, zy, r0, r1, fl);
             uint32_t fd = 0;
@@ -1409,7 +1400,7 @@ struct SpNtItem {
             fl += 3 * NP;
             Z0 = zx;
         } else {
-            phase_eval<NC>(o, e, pp.K, w0, fl, zx);
+            phase_eval_sum<NC>(o, e, pp.K, w0, s0, fl, zx);
             zx = o.Z;
             phase_derivs<NC>(F, o, e, pp.K, fl);
 #pragma unroll
@@ -1420,7 +1411,7 @@ struct SpNtItem {
             Z0 = o.Z;
 #pragma unroll
             for (int i = 0; i < NC; ++i) r0[i] = o.lnphi[i];
-            phase_eval<NC>(o, e, pp.K, w1, fl, zy);
+            phase_eval_sum<NC>(o, e, pp.K, w1, s1, fl, zy);
             zy = o.Z;
             phase_derivs<NC>(F, o, e, pp.K, fl);
 #pragma unroll
