@@ -47,28 +47,6 @@ struct BwdArgs {
     double *kpart;     // npair*n contributions (pair-major) when reduced
 };
 
-// Forks the work of one call from the caller's stream onto side streams and
-// joins it back.  stream(0) is the caller's stream; the side streams come from a
-// bounded set per device that is created on first use and kept, and a call holds
-// its set (locked) while it enqueues.  A call under stream capture, and one for
-// which no set can be had, gets one stream only.
-struct SideSet;
-class StreamFork {
-public:
-    static constexpr int kMax = 4;   // the caller's stream and three side streams
-    StreamFork(hipStream_t s, int want);   // want: streams to use, at most kMax
-    ~StreamFork();                         // joins what has not been joined
-    StreamFork(const StreamFork &) = delete;
-    StreamFork &operator=(const StreamFork &) = delete;
-    int count() const { return n_; }
-    hipStream_t stream(int k) const;
-    int join();   // the caller's stream waits for every side stream
-private:
-    hipStream_t s_;
-    SideSet *set_;
-    int n_;
-};
-
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Per-nc launchers (flash_launch.hpp).  PM (props_per_mixture) selects the

@@ -4,7 +4,6 @@
 // the k gradient.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -12,6 +11,7 @@
 
 #include "ptflash.h"
 #include "flash_api.hpp"
+#include "stream_fork.hpp"
 
 namespace ptf {
 
@@ -76,7 +76,6 @@ static int64_t red_chunks(int64_t n) { return (n + kRedChunk - 1) / kRedChunk; }
 // looked up once per device (with that device current) and kept here.
 constexpr size_t kScratchBytes = PTFLASH_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
-constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static void *g_scratch_addr[kMaxDevices] = {};
 
@@ -95,91 +94,9 @@ static int scratch_address(void **out)
     return PTFLASH_OK;
 }
 
-// ---------------------------------------------------------------------------
-// Side streams
-// ---------------------------------------------------------------------------
-
-// Three streams of default priority and the events that order them against the
-// caller's stream.  Held by one call at a time, and only while it enqueues; a
-// call that finds every set taken waits for the launches of the one before it.
-struct SideSet {
-    std::mutex mu;
-    bool made = false, usable = false;
-    hipStream_t st[StreamFork::kMax - 1];
-    hipEvent_t fork, done[StreamFork::kMax - 1];
-};
-constexpr int kSideSets = 4;   // per device
-static SideSet g_side[kMaxDevices][kSideSets];
-static std::atomic<unsigned> g_side_next{0};
-
-static bool make_side_set(SideSet &x)
-{
-    // another thread may be capturing; creating streams here is no part of it
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    bool ok = hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess;
-    for (int k = 0; ok && k < StreamFork::kMax - 1; ++k)
-        ok = hipStreamCreateWithFlags(&x.st[k], hipStreamNonBlocking) == hipSuccess &&
-             hipEventCreateWithFlags(&x.done[k], hipEventDisableTiming) == hipSuccess;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    return ok;
-}
-
-StreamFork::StreamFork(hipStream_t s, int want) : s_(s), set_(nullptr), n_(1)
-{
-    if (want <= 1) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int dev = -1;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
-        hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
-        (void)hipGetLastError();
-        return;
-    }
-    // The first free set: a lone caller always gets the set made first, whose
-    // streams and the caller's own fall on different hardware queues (there are
-    // four).  Where every set is taken, wait for one in turn.
-    for (int k = 0; k < kSideSets && !set_; ++k)
-        if (g_side[dev][k].mu.try_lock()) set_ = &g_side[dev][k];
-    if (!set_) {
-        set_ = &g_side[dev][g_side_next.fetch_add(1) % kSideSets];
-        set_->mu.lock();
-    }
-    if (!set_->made) {
-        set_->made = true;
-        set_->usable = make_side_set(*set_);
-        if (!set_->usable) (void)hipGetLastError();
-    }
-    const int want_side = (want < kMax ? want : kMax) - 1;
-    if (set_->usable && hipEventRecord(set_->fork, s_) == hipSuccess)
-        for (int k = 0; k < want_side; ++k, ++n_)
-            if (hipStreamWaitEvent(set_->st[k], set_->fork, 0) != hipSuccess) break;
-    if (n_ == 1) {
-        (void)hipGetLastError();
-        set_->mu.unlock();
-        set_ = nullptr;
-    }
-}
-
-hipStream_t StreamFork::stream(int k) const { return k == 0 ? s_ : set_->st[k - 1]; }
-
-int StreamFork::join()
-{
-    if (!set_) return PTFLASH_OK;
-    int rc = PTFLASH_OK;
-    for (int k = 0; k + 1 < n_; ++k) {
-        if (hipEventRecord(set_->done[k], set_->st[k]) == hipSuccess &&
-            hipStreamWaitEvent(s_, set_->done[k], 0) == hipSuccess)
-            continue;
-        // the caller's memory must not be in use past its own stream's order
-        rc = PTFLASH_EHIP;
-        (void)hipStreamSynchronize(set_->st[k]);
-    }
-    set_->mu.unlock();
-    set_ = nullptr;
-    return rc;
-}
-
-StreamFork::~StreamFork() { (void)join(); }
+// The streams that the groups of a ragged batch run on beside the caller's, kept until
+// the process ends.
+static SideSets g_side[kMaxDevices];
 
 static void fill_args(FlashArgs &a, const ptflash_problem *p, const ptflash_options *o,
                       const ptflash_result *r)
@@ -611,6 +528,8 @@ static int flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *
     // for the device inside the call and keeps to the caller's stream.)
     // 500,000 mixtures of seven component counts: 16.3 ms one after another, 10.0 ms
     // this way.
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return PTFLASH_EHIP;
     std::vector<char> done(jobs.size(), 0);
     for (size_t left = jobs.size(); left > 0;) {
         std::vector<size_t> round;
@@ -624,7 +543,8 @@ static int flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *
                 used += jobs[k].bytes;
             }
         left -= round.size();
-        StreamFork f(s, o->form == PTFLASH_FORM_PLAIN ? 1 : (int)round.size());
+        const bool fork = o->form != PTFLASH_FORM_PLAIN && dev >= 0 && dev < kMaxDevices;
+        StreamFork f(fork ? &g_side[dev] : nullptr, s, fork ? (int)round.size() : 1);
         double load[StreamFork::kMax] = {};
         for (size_t r = 0; r < round.size(); ++r) {
             const RaggedJob &j = jobs[round[r]];
