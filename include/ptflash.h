@@ -26,7 +26,8 @@
  *  - Arrays are row-major, mixture-major: element (m, i) of an n x nc array
  *    is at m*nc + i; k_ij of a shared set is at i*nc + j.
  *  - Calls enqueue work on `stream` and return; results are valid once the
- *    stream has been synchronised.  The PLAIN form also synchronises the
+ *    stream has been synchronised.  (A ragged call also uses streams of the
+ *    library's, ordered after and before the work on `stream`.)  The PLAIN form also synchronises the
  *    stream inside the call (it reads the active count after every stage
  *    iteration).
  *  - Return value: 0 on success or a PTFLASH_E* code; nothing is printed and
@@ -299,7 +300,13 @@ size_t ptflash_ragged_workspace_bytes(const ptflash_ragged_problem *prob,
  * NULL (keep_factor is not supported here).  Mixtures with nc_of[m] outside
  * [2, ptflash_max_nc()] or a row count off[m+1] - off[m] != nc_of[m] are
  * reported INVALID (label 0, beta = -1, x = y = the raw z row).  The call
- * synchronises the stream once, to read the group sizes. */
+ * synchronises the stream once, to read the group sizes.  Except in the PLAIN
+ * form and under stream capture, it then runs the groups on `stream` and on up
+ * to three streams of the library's: of default priority, on every compute unit
+ * whatever `stream` is limited to, created at the first such call on a device and
+ * kept until the process ends (at most four sets a device).  They start after
+ * the work enqueued on `stream` before the call, and `stream` waits for them
+ * before what is enqueued on it after the call, also when the call fails. */
 int ptflash_flash_ragged(const ptflash_ragged_problem *prob, const ptflash_options *opt,
                          ptflash_result *res, void *workspace, size_t ws_bytes,
                          hipStream_t stream);

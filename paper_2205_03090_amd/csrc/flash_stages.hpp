@@ -184,8 +184,7 @@ struct Outbox {
 };
 
 // How the items below use the lanes of a wavefront.  Solo: an item is one
-// lane's work.  (A team of lanes per item: flash_team.hpp.)  map and its
-// relatives apply a function to every element of a per-component array.
+// lane's work.  (A team of lanes per item: flash_team.hpp.)
 template <bool SHORT_CUBIC, bool SHORT_CUT, bool SHORT_END>
 struct SoloAs {
     static constexpr bool kTeam = false;
@@ -195,12 +194,6 @@ struct SoloAs {
     // logarithms to tell a trivial one.
     static constexpr bool kShortCubic = SHORT_CUBIC, kShortCut = SHORT_CUT,
                           kShortEnd = SHORT_END;
-    template <int NC, class F>
-    static __device__ __forceinline__ void map(double (&v)[NC], F f)
-    {
-#pragma unroll
-        for (int i = 0; i < NC; ++i) v[i] = f(v[i]);
-    }
 };
 using Solo = SoloAs<true, true, true>;
 

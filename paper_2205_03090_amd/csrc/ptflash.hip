@@ -381,9 +381,10 @@ static int64_t ragged_chunk(int64_t n, int form)
     return n < cap ? n : cap;
 }
 
-// Ragged workspace: counters | sorted ids | one uniform chunk (inputs,
-// outputs) | the uniform flash's workspace for that chunk at nc = kMaxNc.
-static size_t ragged_ws_layout(int64_t n, int form, size_t *flash_off)
+// Ragged workspace: counters | sorted ids | the groups' buffers and workspaces, as
+// large as those of one chunk at nc = kMaxNc (inputs, outputs and the uniform
+// flash's workspace).
+static size_t ragged_ws_bytes(int64_t n, int form)
 {
     const size_t ch = (size_t)ragged_chunk(n, form), C = (size_t)kMaxNc;
     size_t b = align256(2 * kBuckets * sizeof(unsigned long long));
@@ -391,7 +392,6 @@ static size_t ragged_ws_layout(int64_t n, int form, size_t *flash_off)
     b += align256(ch * C * 8) * 6 + align256(ch * C * C * 8) + align256(ch * 8) * 3 +
          align256(ch) + align256(ch * PTFLASH_NITERS * 2) + align256(ch * 2) + align256(ch * 4) +
          align256(ch * 8) + align256(ch * C * 8) + align256(ch);
-    *flash_off = b;
     size_t fw = 0;
     if (Dispatch<WsF>::run(kMaxNc, (int64_t)ch, form, &fw) != PTFLASH_OK) return 0;
     return b + fw;
@@ -469,8 +469,7 @@ static int flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *
         return PTFLASH_EINVAL;
     if (!r->label || !r->beta || !r->x || !r->y) return PTFLASH_EINVAL;
     if (o->keep_factor || r->factor) return PTFLASH_EINVAL;
-    size_t foff = 0;
-    const size_t need = ragged_ws_layout(p->n, o->form, &foff);
+    const size_t need = ragged_ws_bytes(p->n, o->form);
     if (!ws || need == 0 || ws_bytes < need) return PTFLASH_EWORKSPACE;
     if (((uintptr_t)ws & 255u) != 0) return PTFLASH_EINVAL;
     const int64_t n = p->n, ch = ragged_chunk(n, o->form);
@@ -732,8 +731,7 @@ size_t ptflash_ragged_workspace_bytes(const ptflash_ragged_problem *p,
                                       const ptflash_options *o)
 {
     if (!p || !o || p->n < 0) return 0;
-    size_t fo = 0;
-    return ragged_ws_layout(p->n, o->form, &fo);
+    return ragged_ws_bytes(p->n, o->form);
 }
 
 int ptflash_flash_ragged(const ptflash_ragged_problem *p, const ptflash_options *o,
