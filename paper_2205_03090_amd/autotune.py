@@ -15,11 +15,11 @@ current entries) and DIR/autotune_gfx950.md (the timings).
   python -m paper_2205_03090_amd.autotune --out DIR --crossover
 
 times, for small and medium batches, the persistent form at its tuned
-launch shape against the fused form (64- and 128-thread blocks) and writes
-DIR/fused_crossover_gfx950.md, the measurement behind the batch size up to
-which a persistent call with the launch shape left to the library runs
-fused (fused_max_n in csrc/flash_launch.hpp).  Sample: uniform_workload(seed
-32000 + nc, alpha 0.5, the same T and P ranges).
+launch shape against the fused form (64- and 128-thread blocks), and what a
+call that leaves the launch shape to the library takes (a team of lanes per
+mixture, a lane pair or the persistent form, by the limits in
+csrc/form_limits.hpp), and writes DIR/fused_crossover_gfx950.md.  Sample:
+uniform_workload(seed 32000 + nc, alpha 0.5, the same T and P ranges).
 The sample for nc is uniform_workload(seed 30000 + nc, alpha 0.5,
 T in [200, 600] K, P in [1e5, 2e7] Pa) with one shared component set, and
 per_mixture_workload_vec(seed 31000 + nc, same distributions) with one set
@@ -148,10 +148,17 @@ CROSS_NC = (3, 5, 8, 12, 16, 20)
 CROSS_N = (1_000, 3_000, 10_000, 30_000, 100_000, 300_000)
 
 
+def default_form(nc: int, n: int, stability: bool = False) -> str:
+    """The form that a call leaving the launch shape to the library takes."""
+    team, fused = (t[int(stability)][nc] for t in form_limits())
+    if n > fused:
+        return "persistent"
+    return "team" if n <= team else "fused"
+
+
 def fused_default(nc: int, n: int) -> bool:
-    """The library's rule (fused_max_n) for a call that leaves the launch
-    shape to it."""
-    return n <= (150_000 if nc <= 8 else 400_000 // nc)
+    """Whether such a flash runs in one launch, with teams or lane pairs."""
+    return default_form(nc, n) != "persistent"
 
 
 def crossover(a):
@@ -166,10 +173,10 @@ def crossover(a):
              "Sample per (nc, n): uniform_workload(seed 32000 + nc, alpha 0.5, T in [200, 600] K, "
              f"P in [1e5, 2e7] Pa, one shared set); median of {a.reps} timed flashes after two "
              "untimed ones (host clock around each call, launch included). The persistent "
-             "form runs at the tuned launch shape; 'default' is the form a call that leaves "
-             "the launch shape to the library takes.", "",
-             "| nc | n | persistent ms | fused ms (64) | fused ms (128) | default | "
-             "default is the faster |", "|---|---|---|---|---|---|---|"]
+             "form runs at the tuned launch shape; 'default' is a call that leaves the launch "
+             "shape to the library, and the form it takes.", "",
+             "| nc | n | persistent ms | fused ms (64) | fused ms (128) | default ms | default | "
+             "default is the fastest |", "|---|---|---|---|---|---|---|---|"]
     for nc in CROSS_NC:
         for n in CROSS_N:
             if n * nc > 2_000_000:
@@ -180,7 +187,8 @@ def crossover(a):
             ms = {}
             for name, kw in (("pers", dict(block=blocks[0][nc])),
                              ("f64", dict(form=_capi.FORM_FUSED, block=64)),
-                             ("f128", dict(form=_capi.FORM_FUSED, block=128))):
+                             ("f128", dict(form=_capi.FORM_FUSED, block=128)),
+                             ("default", {})):
                 out = api.flash(*args, **kw)
                 api.flash(*args, out=out, **kw)
                 ts = []
@@ -191,10 +199,10 @@ def crossover(a):
                     torch.cuda.synchronize()
                     ts.append(time.perf_counter() - t0)
                 ms[name] = 1e3 * float(np.median(ts))
-            fused = fused_default(nc, n)
-            ok = (ms["f64"] <= ms["pers"]) == fused
+            # within 3 %, the spread of such runs
+            ok = ms["default"] <= 1.03 * min(ms["pers"], ms["f64"])
             lines.append(f"| {nc} | {n} | {ms['pers']:.3f} | {ms['f64']:.3f} | "
-                         f"{ms['f128']:.3f} | {'fused' if fused else 'persistent'} | "
+                         f"{ms['f128']:.3f} | {ms['default']:.3f} | {default_form(nc, n)} | "
                          f"{'yes' if ok else 'no'} |")
             print(lines[-1], flush=True)
     os.makedirs(a.out, exist_ok=True)
