@@ -887,6 +887,16 @@ int resident_blocks(const void *kernel, int block, size_t lds = 0)
     return blocks;
 }
 
+// SIMDs of the current device (four per CU), or -1.
+int device_simds()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return -1;
+    return 4 * cus;
+}
 
 // Workspace: counters | per-mixture records | stage lists | (plain form:)
 // item states and two active lists.
@@ -1169,8 +1179,9 @@ int launch_team(const FlashArgs &a, const ptflash_problem *p, void *ws, hipStrea
     char *tail;
     setup_ctx<NC>(c, a, p->n, ws, &tail);
     // one wavefront per SIMD before a wavefront takes a second mixture
-    constexpr int64_t kSimds = 1024;
-    const int64_t need = (p->n + kSimds - 1) / kSimds;
+    const int64_t simds = device_simds();
+    if (simds <= 0) return PTFLASH_EHIP;
+    const int64_t need = (p->n + simds - 1) / simds;
     const int64_t per_wave = need < X::kPerWave ? need : X::kPerWave;
     if (per_wave > 0)
         hipLaunchKernelGGL((stage_team<NC, PM, X>),
