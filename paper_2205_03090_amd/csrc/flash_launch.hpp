@@ -243,12 +243,14 @@ using TailTeam = Team<8, kBlock / 64>;
 // Component counts whose split trust region ends that way.  Measured on whole
 // flashes (us, without / with teams; shared sets unless noted): nc 2
 // 1533 / 1382 at 500,000 mixtures, nc 3 2282 / 2200 at 1,000,000, nc 5 1998 / 1860 and
-// (own sets) 2306 / 2074 at 500,000, nc 7 3487 / 3209 at 1,000,000, nc 8 1893 / 1679 at
-// 200,000, 3830 / 3565 at 1,000,000, and 2420 / 2230 for 500,000 warm starts.  At
+// (own sets) 2306 / 2074 at 500,000, nc 6 1894 / 1819 (own sets 2385 / 2234) at 500,000,
+// nc 7 3487 / 3209 at 1,000,000, nc 8 1893 / 1679 at 200,000, 3830 / 3565 at 1,000,000, and
+// 2420 / 2230 for 500,000 warm starts.  At
 // nc 4 the stage alone just fits the registers of two wavefronts per SIMD, and
 // with the call it spills (3970 / 4510 at 2,000,000; 4024 with one wavefront); from
 // nc 10 on the teams spill as the stage does (2890 / 3015 for a flash and its
-// gradient of 300,000 at nc 10).
+// gradient of 300,000 at nc 10).  nc 9 would gain 3025 / 2795 at 500,000 (own sets
+// 3228 / 3156) and is not taken so far.
 template <int NC>
 constexpr bool team_tail_ok()
 {
@@ -511,7 +513,7 @@ __device__ __forceinline__ void fused_item(const Ctx<NC> &c, uint32_t id, Outbox
 // with teams, lane pairs; shared sets unless noted): nc 3 401 / 374 at 40,000 mixtures,
 // 720 / 660 at 150,000, nc 5 775 / 655 at 60,000, 1486 / 1305 at 150,000, nc 8 830 / 555 at
 // 25,000, 1190 / 810 at 60,000, 1470 / 1225 at 100,000, nc 10 1380 / 1046 at 60,000, nc 12 (own
-// sets) 3140 / 2306 at 60,000; but nc 16 6715 / 7540 and nc 20 10,810 / 12,280 at 40,000.
+// sets) 2945 / 2351 at 60,000; but nc 16 6715 / 7540 and nc 20 10,810 / 12,280 at 40,000.
 template <int NC>
 constexpr bool fused_tail_ok()
 {
